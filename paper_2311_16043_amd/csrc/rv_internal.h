@@ -71,37 +71,70 @@ inline BvhLayout bvh_layout(int64_t n) {
     return L;
 }
 
-// Radix sort tiling: one wave64 per block, 32 rounds of 64 keys per tile.
-constexpr int kSortWave = 64;
-constexpr int kSortItems = 32;
-constexpr int kSortTile = kSortWave * kSortItems;
-constexpr int kSortAhead = 4;  // items per lane loaded ahead of their ranking
-static_assert(kSortItems % kSortAhead == 0, "sort tile must hold whole load groups");
-constexpr int kBoundsBlocks = 1024;
+// Radix sort: seven 9-bit digits of the 63-bit keys.
+constexpr int kDigitBits = 9, kDigits = 1 << kDigitBits, kPasses = 7;
+static_assert(kDigitBits * kPasses == 63, "the passes must cover the keys");
+constexpr int kSortThreads = 1024;
+// Up to this many Gaussians one block sorts in LDS. The whole build so / by tiles:
+// 45 / 78 us at 2,000, 82 / 100 us at 8,000; beyond, the single CU's ranking
+// outweighs the fourteen launches saved.
+constexpr int64_t kSmallSort = 8 * kSortThreads;
+// Tiles of kSortThreads items each thread `items`, counted in groups of `group`
+// tiles. Small tiles spread the sort over more CUs, large ones write longer runs
+// and read fewer totals (every tile reads those of all groups). Build in us with
+// 1 / 2 items: 97 / 102 at 12,000, 114 / 119 at 100,000, 141 / 142 at 200,000,
+// 187 / 167 at 300,000; with 2 / 4 / 8: 202 / 219 / 300 at 520,000,
+// 328 / 308 / 392 at 1M, 926 / 844 / 851 at 3M, 1,452 / 1,331 / 1,295 at 5M.
+struct SortPlan {
+    int items, group;
+    int64_t tiles;
+};
+inline SortPlan sort_plan(int64_t n) {
+    SortPlan p;
+    p.items = n <= (int64_t(1) << 17) ? 1 : n <= (int64_t(3) << 18) ? 2 : n <= (int64_t(1) << 22) ? 4 : 8;
+    p.tiles = (n + (int64_t)kSortThreads * p.items - 1) / ((int64_t)kSortThreads * p.items);
+    p.group = p.items <= 4 ? 4 : 8;
+    while ((p.tiles + p.group - 1) / p.group > 256) p.group *= 2;
+    return p;
+}
 
-// Leaves per block box of the refit (unions of consecutive sorted leaves).
-constexpr int64_t kBoxBlock = 256;
+// Blocks of the means' bounds.
+constexpr int kBoundsBlocks = 512;
 
-// Counts per segment of the radix sort's two-level prefix sum.
-constexpr int64_t kScanSeg = 1024;
+// Leaves and nodes per block of the leaf, node and refit kernels; the leaves of
+// one such block are the largest group of the box pyramid.
+constexpr int kBoxBlock = 512;
+// Sorted keys, and leaf boxes, held in LDS around a block of nodes.
+constexpr int kKeyWindow = 3 * kBoxBlock, kBoxWindow = 2 * kBoxBlock;
+// Largest power-of-two window of leaf boxes that a block of nodes builds.
+constexpr int kTopWindow = 8;
+// Above this many Gaussians the inputs of a leaf are gathered from packed records,
+// written while the means are read for their bounds: one 64-byte line in the
+// place of five partly used ones. Unpacked / packed: refit of 1.2M 211 / 178 us,
+// build of 300,000 169 / 167 us, of 130,000 123 / 125 us (the inputs then fit
+// the L2s).
+constexpr int64_t kPackFrom = int64_t(1) << 18;
 
 struct BuildWsLayout {
-    size_t keys_tmp, vals_tmp, hist, seg, bounds, block_box, total;
-    int64_t nblocks, nseg;
+    size_t keys_tmp, vals_tmp, before, totals, bounds, box8, box64, box512, node_box, topo, packed, total;
 };
 
 inline BuildWsLayout build_ws_layout(int64_t n) {
     BuildWsLayout W{};
     size_t nn = (size_t)(n > 0 ? n : 1);
-    W.nblocks = (int64_t)((nn + kSortTile - 1) / kSortTile);
+    const SortPlan plan = sort_plan((int64_t)nn);
     size_t off = 0;
     W.keys_tmp = off; off = align_up(off + nn * 8);
     W.vals_tmp = off; off = align_up(off + nn * 4);
-    W.hist = off; off = align_up(off + 256 * (size_t)W.nblocks * 4);
-    W.nseg = (256 * W.nblocks + kScanSeg - 1) / kScanSeg;
-    W.seg = off; off = align_up(off + (size_t)W.nseg * 4);
+    W.before = off; off = align_up(off + (size_t)plan.tiles * kDigits * 4);
+    W.totals = off; off = align_up(off + (size_t)((plan.tiles + plan.group - 1) / plan.group) * kDigits * 4);
     W.bounds = off; off = align_up(off + kBoundsBlocks * 6 * sizeof(float));
-    W.block_box = off; off = align_up(off + (size_t)((nn + kBoxBlock - 1) / kBoxBlock) * 6 * sizeof(float));
+    W.box8 = off; off = align_up(off + (nn + 7) / 8 * 6 * sizeof(float));
+    W.box64 = off; off = align_up(off + (nn + 63) / 64 * 6 * sizeof(float));
+    W.box512 = off; off = align_up(off + (nn + 511) / 512 * 6 * sizeof(float));
+    W.node_box = off; off = align_up(off + nn * 6 * sizeof(float));
+    W.topo = off; off = align_up(off + nn * 16);
+    W.packed = off; off = align_up(off + ((int64_t)nn > kPackFrom ? nn * 64 : 0));
     W.total = off;
     return W;
 }
@@ -130,6 +163,16 @@ __device__ __forceinline__ f3 cross(f3 a, f3 b) {
 
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
+constexpr int kXcds = 8;
+
+// Renumber blocks so that the blocks dispatched to XCD x (b % 8 == x) form a
+// contiguous range of logical blocks. A bijection on [0, nb).
+__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
+    const int64_t q = nb / kXcds, r = nb % kXcds;
+    const int64_t x = b % kXcds;
+    return x * q + (x < r ? x : r) + b / kXcds;
+}
+
 // Header word 12 of a BVH blob holds the number of Gaussians it was built
 // over. Every kernel that reads a tree compares it with the caller's n before
 // touching anything else in the blob (the section offsets follow from n), so a
@@ -137,18 +180,6 @@ __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 // a refit leaves the blob as it was.
 __device__ __forceinline__ bool tree_matches(const float *__restrict__ header, int64_t n) {
     return __float_as_int(header[12]) == (int)(n & 0x7fffffff);
-}
-
-// Mask of the lanes whose `digit` equals this lane's, among `valid` lanes
-// (eight ballots, one per digit bit).
-__device__ __forceinline__ uint64_t match_digit8(uint32_t digit, uint64_t valid) {
-    uint64_t peers = valid;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        uint64_t m = __ballot((digit >> b) & 1u);
-        peers &= ((digit >> b) & 1u) ? m : ~m;
-    }
-    return peers;
 }
 
 }  // namespace rv

@@ -27,16 +27,6 @@ namespace {
 
 constexpr int kTraceBlock = 256;
 constexpr int kWavesPerBlock = kTraceBlock / 64;
-constexpr int kXcds = 8;
-
-// Renumber blocks so that the blocks dispatched to XCD x (b % 8 == x) form a
-// contiguous range of logical blocks. A bijection on [0, nb).
-__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
-    const int64_t q = nb / kXcds, r = nb % kXcds;
-    const int64_t x = b % kXcds;
-    return x * q + (x < r ? x : r) + b / kXcds;
-}
-
 // Logical block of dispatched block b in rounds of kXcds chunks of C
 // consecutive logical blocks: XCD x (b % 8 == x) takes chunk x of each round,
 // so the XCDs walk the logical order side by side (each on a compact part of
