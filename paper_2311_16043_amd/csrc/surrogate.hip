@@ -1202,11 +1202,12 @@ extern "C" size_t rv_surrogate_train_workspace_bytes(int32_t batch) {
     return train_ws(batch).total;
 }
 
-// Inference scratch: [0, 256) the fallback count (byte 0) and the tracer's
-// eight queue counters (byte 64); the list of q_count int64; q_count flags.
+// Inference scratch: the fallback count (256 bytes); the tracer's queue counters;
+// the list of q_count int64; q_count flags.
+constexpr size_t kInferList = kAlign + kQueueBytes;
 extern "C" size_t rv_surrogate_infer_workspace_bytes(int64_t q_count) {
     if (q_count < 0) return 0;
-    return kAlign + align_up((size_t)q_count * sizeof(int64_t)) + align_up((size_t)q_count);
+    return kInferList + align_up((size_t)q_count * sizeof(int64_t)) + align_up((size_t)q_count);
 }
 
 extern "C" rv_status rv_surrogate_init(void *params, uint64_t seed, const float *box_lo_host, const float *box_hi_host,
@@ -1335,9 +1336,9 @@ extern "C" rv_status rv_surrogate_infer(const void *params, const void *bvh, con
     const SurLayout L = sur_layout();
     hipStream_t s = (hipStream_t)stream;
     unsigned long long *count = at<unsigned long long>(ws, 0);
-    unsigned long long *queues = at<unsigned long long>(ws, 64);
-    int64_t *list = at<int64_t>(ws, kAlign);
-    uint8_t *flag = at<uint8_t>(ws, kAlign + align_up((size_t)q_count * sizeof(int64_t)));
+    unsigned long long *queues = at<unsigned long long>(ws, kAlign);
+    int64_t *list = at<int64_t>(ws, kInferList);
+    uint8_t *flag = at<uint8_t>(ws, kInferList + align_up((size_t)q_count * sizeof(int64_t)));
     hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, s, reinterpret_cast<float *>(count), (int64_t)2, 0.0f);
     FwdArgs fa{};
     fa.master = at<float>(params, L.master);

@@ -6,9 +6,9 @@
 // Work mapping. Rays come in pools (see the pooled traversal below): 64
 // Gaussians adjacent in Morton (sorted-leaf) order times one direction for the
 // persistent all-ray kernel (which also serves the SH projection), times a
-// chunk of 4 consecutive directions for the adjoint kernel, and 256
-// consecutive entries for the list kernel. The all-ray forward runs a
-// persistent grid that takes pools from eight queues, one per XCD, each a
+// chunk of 4 consecutive directions for the adjoint kernel, and 64 or 256
+// consecutive entries for the list kernel. Up to kOnePoolWaves pools the all-ray
+// forward gives every wave one; beyond, it runs a persistent grid that takes pools from eight queues, one per XCD, each a
 // contiguous eighth of the Morton order, so each L2 sees a compact part of the
 // tree; a wave whose queue is spent takes pools from the others, so no XCD
 // idles while another still holds work. A wave keeps its lanes supplied
@@ -25,7 +25,6 @@
 namespace rv {
 namespace {
 
-constexpr int kTraceBlock = 256;
 constexpr int kWavesPerBlock = kTraceBlock / 64;
 // Logical block of dispatched block b in rounds of kXcds chunks of C
 // consecutive logical blocks: XCD x (b % 8 == x) takes chunk x of each round,
@@ -52,20 +51,29 @@ constexpr int kAdjChunk = 64;
 // A wave drains pools of rays (64 Gaussians adjacent in sorted order times
 // some directions, or consecutive list entries). Lanes that have no ray take
 // the pool's next rays (ballot + popcount). Each iteration, lanes with
-// traversal work and room in their leaf FIFO visit one node, appending hit
-// leaves instead of testing them; the leaf test then runs as one block for
+// traversal work and room in their leaf FIFO visit one node, appending pairs of
+// hit leaves instead of testing them; the leaf test then runs as one block for
 // all lanes with a pending leaf once enough of them have one, so the
 // expensive exact test executes with most lanes active instead of inside
 // every node step. Leaves are tested in discovery (FIFO) order, so each ray's
 // product, and its early exit, do not depend on which pool the ray was drained
 // from: the all-ray, ray-list, SH and adjoint paths give a ray the same bits.
+//
+// A filled chip is bound by two things at once: the vector-memory path returns
+// about one 16-byte lane load per CU and cycle (340 a ray at 300,000 Gaussians),
+// and the SIMDs issue instructions in nearly nine of ten cycles. Stacks and queues
+// of pairs and the byte-permuted planes took the instructions of a wave's
+// iteration from 321 to 275 (40.6 -> 39.8 ms at 300,000 x 256, 77.2 -> 68.0 ms at
+// 3M x 16 together with the grid sizes below). Records fetched by the quad through
+// LDS made a third of the vector-L1 accesses and ran slower (44.9 ms for the nodes,
+// 49.0 for the leaves, 50.0 for both): direct loads into LDS return no faster, and
+// their addresses are more instructions.
 constexpr int kPoolS = 4;
-constexpr int kFifo = 8;
 constexpr int kPoolRing = 8;
-// The persistent all-ray and list kernels keep 16 stack entries per lane in
-// LDS (24 KB per block with the FIFO, six blocks per CU): fewer deep entries
-// go to the private spill array than with 8 (54.3 against 58.6 ms at object
-// scale). The adjoint kernel, whose gradient table leaves no room, keeps 8.
+// The all-ray and list kernels keep 16 stack entries per lane in LDS (24 KB per
+// block with the FIFO): fewer deep entries go to the private spill array than with
+// 8 (39.8 against 40.5 ms at object scale). The adjoint kernel, whose gradient
+// table leaves no room, keeps 8.
 constexpr int kStreamRing = 16;
 // Directions per pool of the persistent all-ray kernel. With one, the pools
 // in flight on an XCD cover the fewest Gaussians (about 256 against 1,024
@@ -80,6 +88,22 @@ constexpr int kLeafMin = 32;
 // of traversal and saves most of those setups (object scale: 43.6 -> 40.4 ms,
 // adjoint 59.7 -> 58.2 ms).
 constexpr int kRefillMin = kRefillShallow;
+
+// Resident blocks per CU of the persistent traversal. Its waves share the CU's
+// vector-memory path, which they keep full, and the caches: more of them only thin
+// those out, and with few pools they also end further apart. 5 / 4 / 3 blocks:
+// 40.0 / 42.0 / 50.3 ms at 300,000 Gaussians x 256, 59.2 / 58.4 / 69.0 ms at
+// 1.2M x 64, 77.1 / 67.5 / 79.6 ms at 3M x 16; 4.48 / 4.76 / 5.44 ms at
+// 100,000 x 128, 1.16 / 1.17 / 1.23 ms at 50,000 x 64, 774 / 744 / 743 us at
+// 30,000 x 64 (six: 43.8 ms at 300,000 x 256).
+constexpr int kStreamBlocksPerCu = 5, kStreamBlocksDeep = 4, kStreamBlocksFew = 3;
+constexpr int64_t kFewPools = 40000, kDeepStreamGaussians = int64_t(1) << 20;
+// Up to this many pools every wave takes one pool and the hardware hands out the
+// blocks. The queues' counters, on few lines, serve about one wave in 50 ns: with
+// queues / so, 463 / 202 us at 5,003 x 33 (2,607 pools), 629 / 112 us at 5,000 x 64,
+// 540 / 470 us at 20,000 x 64, 726 / 790 us at 30,000 x 64 (the lanes of a wave
+// that has one pool idle towards its end).
+constexpr int64_t kOnePoolWaves = 24000;
 
 struct PoolMap {
     int64_t n;
@@ -104,62 +128,17 @@ inline PoolMap make_pool(int64_t n, int K) {
     return pm;
 }
 
-// One node visit of a pooled ray: hit leaves are appended to the lane's FIFO
-// (slot order), the first hit internal child becomes the next node and the
-// others are stacked to come off in slot order. The stack holds at most three
-// siblings per wide level above the node, so in a tree of the bounded depth a
-// visit starts with room for its three pushes; a malformed tree (visit budget
-// spent, less room than that) ends the ray with NaN.
-template <bool kCount, int kRing>
-__device__ __forceinline__ void pool_node_step(const float4 *__restrict__ nodes4, f3 o, f3 inv, float tmin,
-                                               int32_t &node, int32_t &budget, RingStack<kRing> &st,
-                                               int32_t *my_fifo, int fhead, int &fcount, float &T, int64_t &cn) {
-    if (--budget < 0) {
-        node = -1;
-        fcount = 0;
-        T = __int_as_float(0x7fc00000);
-        return;
-    }
-    int32_t id[4];
-    visit4(nodes4, node, o, inv, tmin, id);
-    if (kCount) ++cn;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        if (is_leaf(id[s])) {
-            my_fifo[((fhead + fcount) & (kFifo - 1)) * kTraceBlock] = ~id[s];
-            ++fcount;
-        }
-    }
-    int32_t nxt = -1;
-    const bool overflow = st.sp > kMaxStack - 3;
-    if (!overflow) {
-#pragma unroll
-        for (int s = 3; s >= 0; --s) {
-            if (id[s] >= 0) {
-                if (nxt >= 0) st.push(nxt);
-                nxt = id[s];
-            }
-        }
-    }
-    if (overflow) {
-        node = -1;
-        fcount = 0;
-        T = __int_as_float(0x7fc00000);
-    } else if (nxt >= 0) {
-        node = nxt;
-    } else if (!st.empty()) {
-        node = st.pop();
-    } else {
-        node = -1;
-    }
-}
+// Visits that a walk makes at most between two looks at its budget (a malformed
+// tree with a cycle ends then, with NaN).
+constexpr uint32_t kBudgetLook = 64;
 
 // Wave-level leaf phase condition: enough lanes hold a pending leaf, or some
 // lane cannot walk for lack of FIFO room, or no lane can walk.
-__device__ __forceinline__ bool leaf_phase_now(bool has, int32_t node, int fcount) {
-    const uint64_t pend = __ballot(has && fcount > 0);
-    const uint64_t blocked = __ballot(has && fcount > kFifo - 4);
-    const uint64_t trav = __ballot(has && node >= 0 && fcount <= kFifo - 4);
+template <int kRing>
+__device__ __forceinline__ bool leaf_phase_now(const Walk<kRing> &wk) {
+    const uint64_t pend = __ballot(wk.queued());
+    const uint64_t blocked = __ballot(!wk.room());
+    const uint64_t trav = __ballot(wk.can_walk());
     return pend != 0 && (__popcll(pend) >= kLeafMin || blocked != 0 || trav == 0);
 }
 
@@ -175,10 +154,13 @@ struct RaySetup {
 
 // Pools handed to one wave. XcdQueue: the pools are cut into kXcds
 // contiguous ranges, one per XCD, each drained one pool at a time through an
-// atomic counter (zero at launch). A wave takes from its own XCD's range
+// atomic counter (zero at launch; kQueueStride words apart, as two on one line
+// slow each other down). A wave takes from its own XCD's range
 // first, so that adjacent Gaussians share that XCD's L2; once the range is
 // spent it takes from the other ranges in turn, so no XCD idles while another
-// still holds work. RangeQueue: a fixed run of consecutive pools.
+// still holds work.
+// RangeQueue: a fixed run of consecutive pools.
+constexpr int kQueueStride = 4;   // the eight counters fill 256 bytes
 struct XcdQueue {
     unsigned long long *ctrs;  // kXcds counters
     int64_t n_pools;
@@ -196,10 +178,10 @@ struct XcdQueue {
         while (turn < kXcds) {
             const int x = (home + turn) % kXcds;
             unsigned long long t = 0;
-            if (lane == __builtin_amdgcn_readfirstlane(lane)) t = atomicAdd(ctrs + x, 1ull);
-            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)t);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(t >> 32));
-            p = n_pools * x / kXcds + (int64_t)(((uint64_t)hi << 32) | lo);
+            if (lane == __builtin_amdgcn_readfirstlane(lane)) t = atomicAdd(ctrs + kQueueStride * x, 1ull);
+            const uint32_t tl = __builtin_amdgcn_readfirstlane((uint32_t)t);
+            const uint32_t th = __builtin_amdgcn_readfirstlane((uint32_t)(t >> 32));
+            p = n_pools * x / kXcds + (int64_t)(((uint64_t)th << 32) | tl);
             if (p < n_pools * (x + 1) / kXcds) return true;
             ++turn;
         }
@@ -216,43 +198,48 @@ struct RangeQueue {
 };
 
 // Trace the rays of the pools the queue hands out with the lanes of one
-// wave. Once c.refill lanes are without a ray (or no lane has one), those
+// wave. With kAhead the words of a lane's next node are fetched as soon as the
+// node is known, while leaves are tested: for launches that leave the chip's
+// memory path idle (5,000 Gaussians x 33: 202 against 210 us; a filled chip runs up
+// to 5 % slower so). Once c.refill lanes are without a ray (or no lane has one), those
 // lanes take the next rays of the current pool; when the pool is spent the
 // wave takes the next pool at once, so lanes stay supplied across pool
 // boundaries. A finished
 // ray writes its T to out[r.out] (when out is given). stk and my_fifo are
 // this lane's columns of the block's LDS stack ring and leaf FIFO.
-template <bool kCount, class Queue, class Pools>
+template <bool kCount, bool kAhead, class Queue, class Pools>
 __device__ __forceinline__ void stream_rays(const float4 *__restrict__ nodes4, const float4 *__restrict__ rec,
                                             const Cuts &c, int64_t n, Queue &queue, Pools &pools,
-                                            int32_t *stk, int32_t *my_fifo, float *__restrict__ out, int64_t &cn,
+                                            Pair *stk, Pair *my_fifo, float *__restrict__ out, int64_t &cn,
                                             int64_t &cl, int64_t &ch) {
     const int lane = threadIdx.x & 63;
     const uint64_t lt = (1ull << lane) - 1ull;
-    RingStack<kStreamRing> st;
-    int32_t spill[RingStack<kStreamRing>::kSpill];
-    st.lds = stk;
-    st.spill = spill;
-    st.stride = kTraceBlock;
-    st.sp = 0;
-    int fhead = 0, fcount = 0;
-    bool has = false;
+    Walk<kStreamRing> wk;
+    Pair spill[Walk<kStreamRing>::kSpill];
+    wk.init(stk, my_fifo, spill);
     int64_t dst = 0;  // output position of the current ray
-    f3 o = mk(0.f, 0.f, 0.f), d = o, inv = o;
+    RayBox rb;
+    rb.set(mk(0.f, 0.f, 0.f), mk(0.f, 0.f, 0.f));
+    f3 d = mk(0.f, 0.f, 0.f);
     float tmin = 0.f, T = 1.f;
-    int32_t self = -1, self_leaf = -1, node = -1;
-    int32_t budget = 0;  // node visits left (n <= 2^30)
+    int32_t self = -1, self_leaf_m1 = -2;
     NoHit none;
+    uint4 ahead[3] = {};   // kAhead: the words of wk.node
+    auto node_words = [&](uint4 (&w)[3]) {
+        const uint4 *r = reinterpret_cast<const uint4 *>(nodes4) + 4 * (int64_t)wk.node + 4;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w[k] = r[k];
+    };
     // wave-uniform pool state
     int next = 0, pool_n = 0;
     bool more = true;
 
-    while (true) {
+    for (uint32_t round = 1;; ++round) {
         // refill idle lanes, moving on to further pools while lanes are idle;
         // only once c.refill lanes are idle (or none holds a ray), so that
         // the ray setup runs for several lanes at a time
-        uint64_t need = __ballot(!has);
-        if (__popcll(need) < c.refill && __ballot(has) != 0) need = 0;
+        uint64_t need = __ballot(wk.idle());
+        if (__popcll(need) < c.refill && ~need != 0) need = 0;
         while (need != 0 && more) {
             if (next >= pool_n) {
                 int64_t p;
@@ -262,56 +249,59 @@ __device__ __forceinline__ void stream_rays(const float4 *__restrict__ nodes4, c
                 continue;
             }
             const int idx = next + __popcll(need & lt);
-            if (!has && idx < pool_n) {
+            if (wk.idle() && idx < pool_n) {
                 const RaySetup r = pools(idx);
-                o = r.o;
                 d = r.d;
-                inv = safe_inv(d);
+                rb.set(r.o, d);
                 tmin = r.tmin;
                 self = r.self;
-                self_leaf = r.self_leaf;
+                self_leaf_m1 = r.self_leaf - 1;
                 T = r.valid ? 1.0f : __int_as_float(0x7fc00000);
-                st.sp = 0;
-                fhead = 0;
-                fcount = 0;
-                node = r.valid && n > 1 ? 0 : -1;
-                budget = (int32_t)n;
+                wk.start(n, r.valid);
+                if (kAhead && wk.node > Walk<kStreamRing>::kDone) node_words(ahead);
                 dst = r.out;
-                has = true;
             }
             next += __popcll(need);
-            need = __ballot(!has);
+            need = __ballot(wk.idle());
         }
-        if (__ballot(has) == 0) break;  // queue spent, every ray finished
+        if (__ballot(!wk.idle()) == 0) break;  // queue spent, every ray finished
 
         // node phase: one four-wide node per lane with traversal work and FIFO
-        // room for all four children
-        if (has && node >= 0 && fcount <= kFifo - 4)
-            pool_node_step<kCount>(nodes4, o, inv, tmin, node, budget, st, my_fifo, fhead, fcount, T, cn);
+        // room for the leaves of both sides
+        if (wk.can_walk()) {
+            if (kAhead) {
+                wk.visit(ahead, rb, tmin, T);
+                if (wk.node > Walk<kStreamRing>::kDone) node_words(ahead);
+            } else {
+                uint4 w[3];
+                node_words(w);
+                wk.visit(w, rb, tmin, T);
+            }
+            if (kCount) ++cn;
+        }
 
         // leaf phase: test one pending leaf per lane when enough lanes have one,
         // when a lane cannot traverse for lack of FIFO room, or when no lane can traverse
-        if (leaf_phase_now(has, node, fcount)) {
-            if (has && fcount > 0) {
-                const int32_t leaf = my_fifo[fhead * kTraceBlock];
-                fhead = (fhead + 1) & (kFifo - 1);
-                --fcount;
-                const float f = leaf_factor(rec, leaf, o, d, tmin, self, self_leaf, c, none, T);
+        if (leaf_phase_now(wk)) {
+            if (wk.queued()) {
+                const int32_t m1 = wk.next_leaf();
+                const float f = leaf_factor(rec, m1, rb.o, d, tmin, self, self_leaf_m1, c, none, T);
                 if (kCount) {
                     ++cl;
                     ch += (f != 1.0f);
                 }
                 T *= f;
-                if (T < c.T_stop) {
-                    node = -1;
-                    fcount = 0;
-                }
+                if (T < c.T_stop) wk.stop();
             }
         }
+        if (round % kBudgetLook == 0 && wk.budget < 0 && !wk.idle()) {
+            T = __int_as_float(0x7fc00000);
+            wk.stop();
+        }
 
-        if (has && node < 0 && fcount == 0) {
+        if (wk.finished()) {
             if (out) out[dst] = T;
-            has = false;
+            wk.node = Walk<kStreamRing>::kIdle;
         }
     }
 }
@@ -425,23 +415,25 @@ struct ListSource {
     }
 };
 
-// List pools: pool p covers list entries p * kPoolS * 64 onwards.
+// List pools: pool p covers the kEntries list entries from p * kEntries.
+template <int kEntries>
 struct ListPools : ListSource {
     int64_t total;
     __device__ __forceinline__ int open(int64_t p) {
-        base = p * (kPoolS * 64);
-        return (int)min<int64_t>(kPoolS * 64, total - base);
+        base = p * kEntries;
+        return (int)min<int64_t>(kEntries, total - base);
     }
 };
 
 // The rays of the Gaussians at sorted positions [m_lo, m_hi) (all n K rays
-// for [0, n)) through per-XCD queues of pools. The grid is persistent (a
+// for [0, n)): with kOnePool one pool per wave (consecutive blocks of pools on one
+// XCD), else through per-XCD queues of pools. The grid of the latter is persistent (a
 // multiple of 8 blocks, about what the device holds at once) and block b
 // serves the queue of XCD b % 8 (round-robin dispatch), whose range is a
 // contiguous eighth of the pools: each L2 sees a compact part of the tree
 // until its range is spent and its waves help with the other ranges.
-template <bool kCount>
-__global__ __launch_bounds__(kTraceBlock) void k_trace_stream(const float *__restrict__ header,
+template <bool kCount, bool kOnePool>
+__global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_stream(const float *__restrict__ header,
                                                               const float4 *__restrict__ nodes4,
                                                               const float4 *__restrict__ rec,
                                                               const float4 *__restrict__ origins,
@@ -450,8 +442,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_stream(const float *__res
                                                               unsigned long long *__restrict__ queues,
                                                               float *__restrict__ vis_ray,
                                                               unsigned long long *__restrict__ totals) {
-    __shared__ int32_t stk[kStreamRing * kTraceBlock];
-    __shared__ int32_t fifo[kFifo * kTraceBlock];
+    __shared__ Pair stk[kStreamRing * kTraceBlock];
+    __shared__ Pair fifo[kFifo * kTraceBlock];
     if (!tree_matches(header, n)) {
         // a tree built for another Gaussian set: every ray of the range is NaN
         if (vis_ray) {
@@ -462,7 +454,6 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_stream(const float *__res
         }
         return;
     }
-    const int x = (int)(blockIdx.x % kXcds);
     GridPools pools;
     pools.rec = rec;
     pools.origins = origins;
@@ -479,10 +470,19 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_stream(const float *__res
     pools.k0 = 0;
     pools.inv_nv = 1.0f;
     const int64_t n_pools = ((m_hi - m_lo + 63) / 64) * (int64_t)pools.n_chunks;
-    XcdQueue q;
-    q.init(queues, n_pools, x);
     int64_t cn = 0, cl = 0, ch = 0;
-    stream_rays<kCount>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, vis_ray, cn, cl, ch);
+    if constexpr (kOnePool) {
+        RangeQueue q;
+        q.next = xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + (threadIdx.x >> 6);
+        q.end = min(n_pools, q.next + 1);
+        stream_rays<kCount, true>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, vis_ray, cn, cl,
+                                  ch);
+    } else {
+        XcdQueue q;
+        q.init(queues, n_pools, (int)(blockIdx.x % kXcds));
+        stream_rays<kCount, false>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, vis_ray, cn, cl,
+                                   ch);
+    }
     if (kCount) {
         atomicAdd(totals + 0, (unsigned long long)cn);
         atomicAdd(totals + 1, (unsigned long long)cl);
@@ -499,15 +499,15 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_stream(const float *__res
 // is spent; otherwise wave w takes the run of
 // pools [w R, (w + 1) R).
 template <bool kQueue>
-__global__ __launch_bounds__(kTraceBlock) void k_trace_list(
+__global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_list(
     const float *__restrict__ header, const float4 *__restrict__ nodes4, const float4 *__restrict__ rec, const float *__restrict__ mean,
     const float *__restrict__ normal, const float *__restrict__ log_scale, int64_t n, const float *__restrict__ dirs,
     int K, Cuts c, const int64_t *__restrict__ ids, int64_t n_list, const unsigned long long *__restrict__ count,
     int64_t id_offset, int out_by_value, int64_t run, unsigned long long *__restrict__ queues,
     float *__restrict__ out) {
-    __shared__ int32_t stk[kStreamRing * kTraceBlock];
-    __shared__ int32_t fifo[kFifo * kTraceBlock];
-    constexpr int kPool = kPoolS * 64;
+    __shared__ Pair stk[kStreamRing * kTraceBlock];
+    __shared__ Pair fifo[kFifo * kTraceBlock];
+    constexpr int kPool = kQueue ? kPoolS * 64 : 64;
     const int64_t total = count ? min<int64_t>(n_list, (int64_t)*count) : n_list;
     const int64_t n_pools = (total + kPool - 1) / kPool;
     using Queue = typename std::conditional<kQueue, XcdQueue, RangeQueue>::type;
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_list(
         q.end = min(n_pools, q.next + run);
         if (q.next >= q.end) return;  // wave-uniform
     }
-    ListPools pools;
+    ListPools<kPool> pools;
     pools.mean = mean;
     pools.normal = normal;
     pools.log_scale = log_scale;
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_list(
     pools.total = total;
     pools.tree_ok = tree_matches(header, n);
     int64_t cn = 0, cl = 0, ch = 0;
-    stream_rays<false>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, out, cn, cl, ch);
+    stream_rays<false, !kQueue>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, out, cn, cl, ch);
 }
 
 // vis_mean[i] = (1/K) sum_k vis[i K + k]: one wave per Gaussian, FP64 lane
@@ -750,8 +750,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_backward(
     const float *__restrict__ dirs, PoolMap pm, Cuts c, const float *__restrict__ grad_ray,
     const float *__restrict__ grad_mean_in, const float *__restrict__ vis_fwd, float *go, float *gm, float *gl,
     float4 *ovf_buf, uint32_t *ovf_flags, int ovf_slots, int ovf_cap) {
-    __shared__ int32_t stk[kPoolRing * kTraceBlock];
-    __shared__ int32_t fifo[kFifo * kTraceBlock];
+    __shared__ Pair stk[kPoolRing * kTraceBlock];
+    __shared__ Pair fifo[kFifo * kTraceBlock];
     __shared__ float ogr[kWavesPerBlock][64 * 3];   // origin terms per item
     __shared__ GradTable table;
     // the block's four items (64 Gaussians x a chunk of directions each),
@@ -822,22 +822,16 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_backward(
     src.K = K;
 
     const uint64_t lt = (1ull << lane) - 1ull;
-    RingStack<kPoolRing> st;
-    int32_t spill[RingStack<kPoolRing>::kSpill];
-    st.lds = stk + threadIdx.x;
-    st.spill = spill;
-    st.stride = kTraceBlock;
-    st.sp = 0;
-    int32_t *my_fifo = fifo + threadIdx.x;
-    int fhead = 0, fcount = 0;
-    bool has = false;
+    Walk<kPoolRing> wk;
+    Pair spill[Walk<kPoolRing>::kSpill];
+    wk.init(stk + threadIdx.x, fifo + threadIdx.x, spill);
     int oi = 0, it = 0;  // item and item origin of the current ray
     float gk = 0.f;      // upstream gradient of the current ray
-    f3 o = mk(0.f, 0.f, 0.f), d = o, inv = o;
+    RayBox rb;
+    rb.set(mk(0.f, 0.f, 0.f), mk(0.f, 0.f, 0.f));
+    f3 d = mk(0.f, 0.f, 0.f);
     float tmin = 0.f, T = 1.f;
-    int32_t self = -1, self_leaf = -1, node = -1;
-    int32_t budget = 0;
-    int64_t cn = 0;
+    int32_t self = -1, self_leaf_m1 = -2;
     GradScatter gs;
     gs.active = false;
     gs.g_over = 0.f;
@@ -850,18 +844,10 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_backward(
     gs.ovf_n = &ovf_n;
     gs.ovf_cap = ovf_cap;
     bool drained = false;  // wave-uniform: the block's rays are all handed out
-    auto restart = [&]() {
-        T = 1.0f;
-        st.sp = 0;
-        fhead = 0;
-        fcount = 0;
-        node = pm.n > 1 ? 0 : -1;
-        budget = (int32_t)pm.n;
-    };
 
-    while (true) {
-        const uint64_t need = __ballot(!has);
-        if (need != 0 && !drained && (__popcll(need) >= kRefillMin || __ballot(has) == 0)) {
+    for (uint32_t round = 1;; ++round) {
+        const uint64_t need = __ballot(wk.idle());
+        if (need != 0 && !drained && (__popcll(need) >= kRefillMin || ~need == 0)) {
             // the wave's first active lane reserves one block ray per idle lane
             const int cnt = __popcll(need);
             int base = 0;
@@ -869,7 +855,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_backward(
             base = __builtin_amdgcn_readfirstlane(base);
             if (base + cnt >= total) drained = true;
             const int idx = base + __popcll(need & lt);
-            if (!has && idx < total) {
+            if (wk.idle() && idx < total) {
                 it = (idx >= n_a) + (idx >= n_b) + (idx >= n_c);
                 const int local = idx - (it == 0 ? 0 : it == 1 ? n_a : it == 2 ? n_b : n_c);
                 src.m0 = item_m0[it];
@@ -880,54 +866,53 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_backward(
                 oi = (int)(r.self_leaf - src.m0);
                 // r.out = i K + k: the ray's place in grad_ray and vis_fwd
                 gk = (grad_mean_in ? grad_mean_in[r.self] / (float)K : 0.0f) + (grad_ray ? grad_ray[r.out] : 0.0f);
-                o = r.o;
                 d = r.d;
-                inv = safe_inv(d);
+                rb.set(r.o, d);
                 tmin = r.tmin;
                 self = r.self;
-                self_leaf = r.self_leaf;
-                restart();
+                self_leaf_m1 = r.self_leaf - 1;
                 gs.origin = mk(0.f, 0.f, 0.f);
-                gs.active = vis_fwd != nullptr;
+                // a ray with nothing to propagate ends here
+                gs.active = vis_fwd != nullptr || gk == 0.0f;
                 gs.g_over = vis_fwd ? -gk * vis_fwd[r.out] : 0.0f;
-                if (gk == 0.0f) {   // nothing to propagate: the ray ends here
-                    node = -1;
-                    gs.active = true;
-                }
-                has = true;
+                T = 1.0f;
+                wk.start(pm.n, gk != 0.0f);
             }
         }
-        if (__ballot(has) == 0) break;
+        if (__ballot(!wk.idle()) == 0) break;
 
-        if (has && node >= 0 && fcount <= kFifo - 4)
-            pool_node_step<false>(nodes4, o, inv, tmin, node, budget, st, my_fifo, fhead, fcount, T, cn);
-
-        if (leaf_phase_now(has, node, fcount)) {
-            if (has && fcount > 0) {
-                const int32_t leaf = my_fifo[fhead * kTraceBlock];
-                fhead = (fhead + 1) & (kFifo - 1);
-                --fcount;
-                T *= leaf_factor(rec, leaf, o, d, tmin, self, self_leaf, c, gs, T);
-                if (T < c.T_stop) {
-                    node = -1;
-                    fcount = 0;
-                }
-            }
+        if (wk.can_walk()) {
+            const uint4 *r = reinterpret_cast<const uint4 *>(nodes4) + 4 * (int64_t)wk.node + 4;
+            const uint4 w[3] = {r[0], r[1], r[2]};
+            wk.visit(w, rb, tmin, T);
         }
 
-        if (has && node < 0 && fcount == 0) {
+        if (leaf_phase_now(wk)) {
+            if (wk.queued()) {
+                const int32_t m1 = wk.next_leaf();
+                T *= leaf_factor(rec, m1, rb.o, d, tmin, self, self_leaf_m1, c, gs, T);
+                if (T < c.T_stop) wk.stop();
+            }
+        }
+        if (round % kBudgetLook == 0 && wk.budget < 0 && !wk.idle()) {
+            T = __int_as_float(0x7fc00000);
+            wk.stop();
+        }
+
+        if (wk.finished()) {
             if (!gs.active) {
                 // T_final is known: trace the same ray again, scattering
                 gs.g_over = -gk * T;
                 gs.active = true;
-                restart();
+                T = 1.0f;
+                wk.start(pm.n, true);
             } else {
                 if (gs.origin.x != 0.f || gs.origin.y != 0.f || gs.origin.z != 0.f) {
                     atomicAdd(&ogr[it][3 * oi + 0], gs.origin.x);
                     atomicAdd(&ogr[it][3 * oi + 1], gs.origin.y);
                     atomicAdd(&ogr[it][3 * oi + 2], gs.origin.z);
                 }
-                has = false;
+                wk.node = Walk<kPoolRing>::kIdle;
             }
         }
     }
@@ -990,6 +975,12 @@ __global__ __launch_bounds__(64) void k_fill_u32_trace(uint32_t *__restrict__ p,
     for (int64_t i = threadIdx.x; i < count; i += 64) p[i] = v;
 }
 
+// The counters of the XCD queues (kQueueBytes) to zero.
+void launch_clear_queues(unsigned long long *queues, hipStream_t s) {
+    hipLaunchKernelGGL(k_fill_u32_trace, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t *>(queues),
+                       (int64_t)(kQueueBytes / 4), 0u);
+}
+
 inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
 rv_status validate_trace(const char *fn, const void *bvh, const rv_gaussians *g, const float *dirs, int32_t K,
@@ -1011,42 +1002,41 @@ rv_status validate_trace(const char *fn, const void *bvh, const rv_gaussians *g,
 }
 
 
-// Resident blocks per CU of the persistent traversal. Every wave in flight
-// keeps its pools' part of the tree in the XCD's L2, so more waves hide more
-// latency but thin the L2 out; six blocks (24 waves) per CU gave the shortest
-// object-scale trace (58.8 ms, against 63.0 at the eight the registers allow
-// and 68.0 at four).
-constexpr int kStreamBlocksPerCu = 6;
-
 // Blocks of a persistent traversal grid: what the device holds at once, up
-// to kStreamBlocksPerCu per CU (a multiple of 8, at least 8: every XCD queue
+// to the blocks per CU above (a multiple of 8, at least 8: every XCD queue
 // has blocks), no more than the pools need.
-int64_t stream_blocks(int64_t n_pools) {
+int64_t stream_blocks(int64_t n_pools, int64_t n) {
     static std::atomic<int> cached[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-    int nb = (dev >= 0 && dev < 64) ? cached[dev].load() : 0;
+    int nb = (dev >= 0 && dev < 64) ? cached[dev].load() : 0;   // 256 CUs + blocks per CU
     if (nb <= 0) {
         int cus = 0, per_cu = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) != hipSuccess ||
             cus <= 0)
             cus = 256;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_trace_stream<false>, kTraceBlock, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_trace_stream<false, false>, kTraceBlock, 0) !=
                 hipSuccess ||
             per_cu <= 0)
             per_cu = 4;
         (void)hipGetLastError();  // a failed query above must not surface as a launch error
-        nb = cus * std::min(per_cu, kStreamBlocksPerCu);
+        nb = cus * 256 + std::min(per_cu, kStreamBlocksPerCu);
         if (dev >= 0 && dev < 64) cached[dev].store(nb);
     }
-    int64_t want = std::min<int64_t>(nb, (n_pools + kWavesPerBlock - 1) / kWavesPerBlock);
+    const int cus = nb / 256;
+    const int per_cu = std::min(nb % 256, n_pools <= kFewPools           ? kStreamBlocksFew
+                                          : n >= kDeepStreamGaussians ? kStreamBlocksDeep
+                                                                      : kStreamBlocksPerCu);
+    int64_t want = std::min<int64_t>((int64_t)cus * per_cu, (n_pools + kWavesPerBlock - 1) / kWavesPerBlock);
     want = (want + kXcds - 1) / kXcds * kXcds;
     return std::max<int64_t>(want, kXcds);
 }
 
-// Waves of the list kernel beyond which each wave takes a run of several
-// pools (about four times what the device holds at once).
-constexpr int64_t kListTargetWaves = 32768;
+// Waves of the list kernel beyond which each wave takes a run of several pools of
+// 64 entries: few full waves end closer together than many that contend for the
+// caches. With 2,048 / 4,096 / 16,384 waves 1.58 / 1.74 / 1.96 ms for 1M random rays
+// (1.82 ms in pools of 256), 433 / 378 / 378 us for 200,000.
+constexpr int64_t kListTargetWaves = 2048;
 
 }  // namespace
 
@@ -1055,13 +1045,12 @@ void launch_trace_list(const void *bvh, const rv_gaussians *g, const float *dirs
                        bool out_by_value, float *out, unsigned long long *queues, hipStream_t stream) {
     if (n_list <= 0) return;
     const BvhLayout L = bvh_layout(g->n);
-    const int64_t pools = (n_list + kPoolS * 64 - 1) / (kPoolS * 64);
+    const int64_t entries = queues ? kPoolS * 64 : 64, pools = (n_list + entries - 1) / entries;
     Cuts cc = c;
     cc.refill = refill_lanes(g->n);
     if (queues) {
-        hipLaunchKernelGGL(k_fill_u32_trace, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t *>(queues),
-                           (int64_t)(2 * kXcds), 0u);
-        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools)), dim3(kTraceBlock), 0, stream,
+        launch_clear_queues(queues, stream);
+        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n)), dim3(kTraceBlock), 0, stream,
                            at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), g->mean,
                            c.dir_mode ? g->normal : nullptr, g->log_scale, g->n, dirs, K, cc, ids, n_list, count,
                            id_offset, out_by_value ? 1 : 0, (int64_t)0, queues, out);
@@ -1098,13 +1087,16 @@ void launch_trace_stream(const void *bvh, const rv_gaussians *g, const float *di
     if (m_hi < 0) m_hi = g->n;
     const int64_t n_pools = ((m_hi - m_lo + 63) / 64) * (int64_t)((K + kStreamPoolS - 1) / kStreamPoolS);
     auto *queues = static_cast<unsigned long long *>(ws);
-    hipLaunchKernelGGL(k_fill_u32_trace, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t *>(queues),
-                       (int64_t)(2 * kXcds), 0u);
     Cuts cc = c;
     cc.refill = refill_lanes(g->n);
-    hipLaunchKernelGGL(k_trace_stream<kCount>, dim3((unsigned)stream_blocks(n_pools)), dim3(kTraceBlock), 0, s,
-                       at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), at<float4>(bvh, L.origins), dirs, g->n,
-                       K, cc, m_lo, m_hi, by_leaf ? 1 : 0, queues, vis_ray, totals);
+    const bool one = n_pools <= kOnePoolWaves;
+    if (!one) launch_clear_queues(queues, s);
+    const unsigned blocks =
+        (unsigned)(one ? (n_pools + kWavesPerBlock - 1) / kWavesPerBlock : stream_blocks(n_pools, g->n));
+    hipLaunchKernelGGL((one ? k_trace_stream<kCount, true> : k_trace_stream<kCount, false>), dim3(blocks),
+                       dim3(kTraceBlock), 0, s, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4),
+                       at<float4>(bvh, L.leaf_rec), at<float4>(bvh, L.origins), dirs, g->n, K, cc, m_lo, m_hi,
+                       by_leaf ? 1 : 0, queues, vis_ray, totals);
 }
 
 // Enqueue the all-ray trace with its scratch at ws (256-byte aligned: the
