@@ -5,10 +5,10 @@
 //
 // Work mapping. Rays come in pools (see the pooled traversal below): 64
 // Gaussians adjacent in Morton (sorted-leaf) order times one direction for the
-// persistent all-ray kernel (which also serves the SH projection), times a
-// chunk of 4 consecutive directions for the adjoint kernel, and 64 or 256
-// consecutive entries for the list kernel. Up to kOnePoolWaves pools the all-ray
-// forward gives every wave one; beyond, it runs a persistent grid that takes pools from eight queues, one per XCD, each a
+// all-ray kernels (the forward, which also serves the SH projection, and the
+// adjoint), and 64 or 256 consecutive entries for the list kernel. Up to
+// kOnePoolWaves pools (kAdjOnePoolWaves in the adjoint) every wave takes one;
+// beyond, a persistent grid takes them from eight queues, one per XCD, each a
 // contiguous eighth of the Morton order, so each L2 sees a compact part of the
 // tree; a wave whose queue is spent takes pools from the others, so no XCD
 // idles while another still holds work. A wave keeps its lanes supplied
@@ -40,12 +40,6 @@ __device__ __forceinline__ int64_t xcd_chunk_block(int64_t b, int64_t nb) {
     return ((r / C) * kXcds + x) * C + r % C;
 }
 
-// Chunk of the adjoint's block order: 64 logical blocks (8 groups of 64
-// Gaussians, every direction) per XCD and round. Against one contiguous eighth
-// of the scene per XCD, the re-tracing adjoint runs 81.5 instead of 90.3 ms at
-// object scale (200k x 128); chunks of 16 / 256 give 82.3 / 85.5 ms.
-constexpr int kAdjChunk = 64;
-
 // ---- pooled traversal -----------------------------------------------------------
 //
 // A wave drains pools of rays (64 Gaussians adjacent in sorted order times
@@ -68,12 +62,12 @@ constexpr int kAdjChunk = 64;
 // LDS made a third of the vector-L1 accesses and ran slower (44.9 ms for the nodes,
 // 49.0 for the leaves, 50.0 for both): direct loads into LDS return no faster, and
 // their addresses are more instructions.
+//
+// Entries of a queued list pool, in waves.
 constexpr int kPoolS = 4;
-constexpr int kPoolRing = 8;
-// The all-ray and list kernels keep 16 stack entries per lane in LDS (24 KB per
-// block with the FIFO): fewer deep entries go to the private spill array than with
-// 8 (39.8 against 40.5 ms at object scale). The adjoint kernel, whose gradient
-// table leaves no room, keeps 8.
+// Stack entries per lane in LDS (24 KB per block with the FIFO): with 16 fewer deep
+// entries go to the private spill array than with 8 (39.8 against 40.5 ms at object
+// scale).
 constexpr int kStreamRing = 16;
 // Directions per pool of the persistent all-ray kernel. With one, the pools
 // in flight on an XCD cover the fewest Gaussians (about 256 against 1,024
@@ -81,14 +75,6 @@ constexpr int kStreamRing = 16;
 // against 53.7 with two and 54.5 with four at object scale.
 constexpr int kStreamPoolS = 1;
 constexpr int kLeafMin = 32;
-// Idle lanes that trigger a refill of a wave in the adjoint, unless no lane
-// holds a ray (the forward kernels take Cuts::refill, set from the tree's
-// size). Refilling at every finished ray ran the ray setup for one or two
-// lanes nearly every iteration; waiting for 12 idle lanes costs a few lanes
-// of traversal and saves most of those setups (object scale: 43.6 -> 40.4 ms,
-// adjoint 59.7 -> 58.2 ms).
-constexpr int kRefillMin = kRefillShallow;
-
 // Resident blocks per CU of the persistent traversal. Its waves share the CU's
 // vector-memory path, which they keep full, and the caches: more of them only thin
 // those out, and with few pools they also end further apart. 5 / 4 / 3 blocks:
@@ -104,29 +90,6 @@ constexpr int64_t kFewPools = 40000, kDeepStreamGaussians = int64_t(1) << 20;
 // 540 / 470 us at 20,000 x 64, 726 / 790 us at 30,000 x 64 (the lanes of a wave
 // that has one pool idle towards its end).
 constexpr int64_t kOnePoolWaves = 24000;
-
-struct PoolMap {
-    int64_t n;
-    int K, n_chunks;
-    int64_t n_items;   // ceil(n / 64) * n_chunks
-    int64_t n_blocks;
-    int64_t w_off;     // first wave of this launch
-};
-
-// Waves per launch: a dispatch counts its work-items in 32 bits, so one grid
-// stays at 2^24 waves (2^30 work-items).
-constexpr int64_t kLaunchWaves = int64_t(1) << 24;
-
-inline PoolMap make_pool(int64_t n, int K) {
-    PoolMap pm;
-    pm.n = n;
-    pm.K = K;
-    pm.n_chunks = (K + kPoolS - 1) / kPoolS;
-    pm.n_items = ((n + 63) / 64) * (int64_t)pm.n_chunks;
-    pm.n_blocks = (pm.n_items + kWavesPerBlock - 1) / kWavesPerBlock;
-    pm.w_off = 0;
-    return pm;
-}
 
 // Visits that a walk makes at most between two looks at its budget (a malformed
 // tree with a cycle ends then, with NaN).
@@ -646,44 +609,41 @@ __global__ __launch_bounds__(256) void k_sh_rows(const float *__restrict__ rows,
 }
 
 // ---- adjoint ----------------------------------------------------------------
+//
+// The adjoint traces as the forward does. A hit leaves a record in the wave's LDS
+// stage: the leaf and four floats, a = (dL/dalpha) alpha and the whitened vector e,
+// from which all seven gradient terms of the hit follow. A full stage is added to
+// accumulators of 32 bytes per Gaussian, eight lanes to a record, so that a record
+// is one request; a second kernel applies what the terms of a Gaussian share
+// (1 / opacity, W^T) and adds the results to the caller's arrays.
+//
+// The bound is the rate of device atomics: 20.9 G requests/s of up to 64 bytes, to
+// whichever addresses and from any number of waves (single floats as many, so the
+// seven terms one by one would take seven times as long). 200,000 x 128 with the
+// forward's T (11.8 hits a ray) takes 15.0 ms without them, 20.5 ms with one per
+// hit, 17.9 ms with the records of a stage chained by leaf first. An LDS table per
+// block of 1,024 rays, seven LDS atomics a hit, makes fewer device atomics but leaves
+// room for three blocks per CU: 46.4 ms; the table filled from records in memory
+// after the block's rays, 35.5 ms, or by a kernel of its own, 39.7 ms (LDS atomics:
+// 30 cycles a hit and CU).
 
-// Per-block accumulation table of the scatter: the four waves of a block
-// trace 64 adjacent origins x 16 directions, whose hits concentrate on the
-// same nearby Gaussians, so their seven sums are added in LDS and flushed
-// with one set of global atomics per Gaussian at the end of the block. Hits
-// whose Gaussian finds no slot are kept as records in a buffer of the block's
-// own; once the table is flushed, a second pass sums the records per Gaussian
-// in the emptied table and flushes it again.
-// A Gaussian tries kHashProbes consecutive slots before its hit goes to the
-// global atomics: once the table has filled, every further probe is a
-// compare-and-swap that cannot succeed (2 / 4 / 8 / 16 probes: 59.5 / 57.7 /
-// 57.8 / 60.9 ms with the forward's T, 88.3 / 90.2 / 94.6 / 104.0 ms
-// re-tracing).
-constexpr int kHashSlots = 1024;
-// Record buffers for the hits that overflow a block's table: more buffers
-// than blocks can be resident (3 per CU), 8,192 records (256 KB) each, 256 MB
-// in all. Against seven device atomics per overflowing hit, the second pass
-// takes the adjoint with the forward's T from 57.3 to 50.6 ms at object scale
-// (200k x 128; 4,096 records: 51.7 ms, 16,384: 51.8 ms; 16 or 32 probes in the
-// second pass: no change).
-constexpr int kOvfSlots = 1024, kOvfCap = 8192;
-constexpr int kHashProbes = 4;
+// Waves of one launch that take a pool each: a dispatch counts its work-items in 32
+// bits, so one grid stays at 2^24 waves (2^30 work-items).
+constexpr int64_t kLaunchWaves = int64_t(1) << 24;
+// Up to this many pools every wave takes one pool (four blocks per CU, so that the
+// next node's words fit the registers): one pool / queues 293 / 361 us at 5,003 x 33
+// (2,607 pools), 309 / 404 us at 10,000 x 64, 784 / 697 us at 20,000 x 64.
+constexpr int64_t kAdjOnePoolWaves = 16000;
+// Records per wave in LDS: as many as leave a CU five blocks; with chains a lane
+// each. A chip that is not filled (kFewPools) is bound by the waves' own time, which
+// chaining adds to: 697 / 784 us without / with at 20,000 x 64, the same at 50,000.
+constexpr int kAdjStageChain = 64, kAdjStage = 88;
+constexpr int32_t kLinked = INT32_MIN;   // the leaf of a record that is not the head of its chain
 
-struct GradTable {
-    int32_t key[kHashSlots];         // Gaussian index, -1 when free
-    float val[7][kHashSlots];        // opacity, mean xyz, log-scale xyz
-
-    // Slot of Gaussian j (claimed if free), or -1 after kHashProbes probes.
-    __device__ __forceinline__ int find(int32_t j) {
-        const uint32_t h = ((uint32_t)j * 2654435761u) >> 22;   // 10 bits
-#pragma unroll
-        for (int p = 0; p < kHashProbes; ++p) {
-            const int s = (int)((h + p) & (kHashSlots - 1));
-            const int32_t k = atomicCAS(&key[s], -1, j);
-            if (k == -1 || k == j) return s;
-        }
-        return -1;
-    }
+// What the adjoint works in (null: every term goes to the caller's arrays at once).
+struct AdjScratch {
+    float *acc;   // [n][8] by leaf: the sums of a, a e and a e^2 (by component)
+    float *org;   // [n][4] by leaf: the origin terms
 };
 
 // Seven sums of Gaussian j added with device-scope atomics.
@@ -696,176 +656,195 @@ __device__ __forceinline__ void add_grad_global(float *go, float *gm, float *gl,
     }
 }
 
-struct GradScatter {
+struct GradRecord {
     bool active;        // false on the pass that only recovers T_final
+    bool keep;          // records are kept; else a hit goes to the caller's arrays at once
     float g_over;       // -(dL/dT) * T_final for the current ray
-    float *go, *gm, *gl;
-    GradTable *table;
     f3 origin;          // accumulated d/d(origin) of the current ray
-    // the block's overflow records (two float4 each: source index and the
-    // seven sums), or null; *ovf_n counts the records claimed (LDS)
-    float4 *ovf;
-    int *ovf_n;
-    int ovf_cap;
+    float *go, *gm, *gl;
+    bool hit;           // the leaf under test left a record:
+    float a;
+    f3 e;
 
     __device__ __forceinline__ void operator()(const LeafHit &h, float) {
         if (!active || h.clamped) return;
         const float ga = g_over / h.one_minus;   // dL/dalpha
-        const float a = ga * h.alpha;
-        const f3 wte = h.e.x * h.w0 + h.e.y * h.w1 + h.e.z * h.w2;   // W^T e
-        const float v[7] = {a / h.opacity, a * wte.x, a * wte.y, a * wte.z,
-                            a * h.e.x * h.e.x, a * h.e.y * h.e.y, a * h.e.z * h.e.z};
-        const int slot = table->find(h.src);
-        if (slot >= 0) {
-#pragma unroll
-            for (int c = 0; c < 7; ++c) atomicAdd(&table->val[c][slot], v[c]);
-        } else {
-            // no slot: keep the hit for the block's second pass when its
-            // record buffer has room, else add it to the gradients at once
-            const int r = ovf ? atomicAdd(ovf_n, 1) : ovf_cap;
-            if (r < ovf_cap) {
-                ovf[2 * r] = make_float4(__int_as_float(h.src), v[0], v[1], v[2]);
-                ovf[2 * r + 1] = make_float4(v[3], v[4], v[5], v[6]);
-            } else {
-                add_grad_global(go, gm, gl, h.src, v);
-            }
-        }
+        a = ga * h.alpha;
+        e = h.e;
+        const f3 wte = e.x * h.w0 + e.y * h.w1 + e.z * h.w2;   // W^T e
         origin = origin - a * wte;
+        hit = keep;
+        if (keep) return;
+        const float v[7] = {a / h.opacity, a * wte.x, a * wte.y, a * wte.z, a * e.x * e.x, a * e.y * e.y, a * e.z * e.z};
+        add_grad_global(go, gm, gl, h.src, v);
     }
 };
 
-// Adjoint over the same pools as the forward (64 Gaussians x a chunk of
-// directions per wave). Each ray with a nonzero upstream gradient
+// A wave's stage of records: (a, e) of a hit of leaf `leaf`, or the origin terms of
+// a ray (in e) of leaf ~leaf.
+template <bool kChain>
+struct AdjStage {
+    static constexpr int kSize = kChain ? kAdjStageChain : kAdjStage;
+    struct Lds {
+        float val[kSize * 4];
+        int32_t leaf[kSize];
+        int32_t next[kChain ? kSize : 1];   // the next record of a chain, -1 at its end
+        int32_t last[kChain ? kSize : 1];   // the last record of a hash class; then the chains' heads
+    };
+    Lds *s;
+    int n;   // wave-uniform
+    // Orders the wave's accesses to its stage.
+    static __device__ __forceinline__ void sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+    // One record from each lane with `has` (called by the whole wave).
+    __device__ __forceinline__ void put(bool has, int32_t m, float a, f3 e, const AdjScratch &sc) {
+        const uint64_t lanes = __ballot(has);
+        const int more = (int)__popcll(lanes);
+        if (more == 0) return;
+        if (n + more > kSize) flush(sc);
+        if (has) {
+            const int r = n + (int)__popcll(lanes & ((1ull << (threadIdx.x & 63)) - 1ull));
+            *reinterpret_cast<float4 *>(s->val + 4 * r) = make_float4(a, e.x, e.y, e.z);
+            s->leaf[r] = m;
+        }
+        n += more;
+    }
+    // Lane c of eight: the c-th sum of record r of leaf m.
+    __device__ __forceinline__ float term(int r, int32_t m, int c, int comp) const {
+        const float a = s->val[4 * r], x = s->val[4 * r + 1 + (m >= 0 ? comp : c & 3)];
+        const float ax = a * x;
+        return m < 0 ? x : c == 0 ? a : c < 4 ? ax : ax * x;
+    }
+    static __device__ __forceinline__ void add(const AdjScratch &sc, int32_t m, int c, float v) {
+        if (c < (m >= 0 ? 7 : 3)) unsafeAtomicAdd((m >= 0 ? sc.acc + 8 * (int64_t)m : sc.org + 4 * (int64_t)~m) + c, v);
+    }
+    // Adds the records, eight lanes to one. With kChain those of one leaf are chained
+    // first (through a hash of 64 classes: one that another leaf has taken starts a
+    // new chain), and each chain is one addition.
+    __device__ __forceinline__ void flush(const AdjScratch &sc) {
+        const int lane = threadIdx.x & 63, c = lane & 7, comp = (c + 2) % 3;
+        sync();
+        if constexpr (kChain) {
+            static_assert(kSize == 64, "a record per lane");
+            const bool live = lane < n;
+            s->last[lane] = -1;
+            sync();
+            const int32_t mine = live ? s->leaf[lane] : 0;
+            const int prev = live ? atomicExch(&s->last[((uint32_t)mine * 2654435761u) >> 26], lane) : -1;
+            const bool linked = prev >= 0 && s->leaf[prev] == mine;
+            s->next[lane] = linked ? prev : -1;
+            sync();
+            if (linked) s->leaf[prev] = kLinked;
+            sync();
+            const bool head = live && s->leaf[lane] != kLinked;
+            const uint64_t heads = __ballot(head);
+            if (head) s->last[__popcll(heads & ((1ull << lane) - 1ull))] = lane;
+            sync();
+            const int n_heads = (int)__popcll(heads);
+            for (int i = lane >> 3; i < n_heads; i += 8) {
+                int r = s->last[i];
+                const int32_t m = s->leaf[r];
+                float sum = 0.0f;
+                do {
+                    sum += term(r, m, c, comp);
+                    r = s->next[r];
+                } while (r >= 0);
+                add(sc, m, c, sum);
+            }
+        } else {
+            for (int r = lane >> 3; r < n; r += 8) {
+                const int32_t m = s->leaf[r];
+                add(sc, m, c, term(r, m, c, comp));
+            }
+        }
+        sync();
+        n = 0;
+    }
+};
+
+// Trace of the adjoint, pools and queues as the forward's. Each ray with a nonzero upstream gradient
 // g = dL/dV_ik (grad_ray) + dL/dVbar_i / K (grad_mean) is traced once to
-// recover T_final (skipped when the forward's T are given), then again with
-// the same visits in the same order, scattering dL/dalpha_j = -g T_final /
-// (1 - alpha_j) into each included, unclamped Gaussian's parameters (through
-// the block's LDS table and its overflow records). The source's own term
-// (through the ray origin) is summed per Gaussian in LDS and added once per
-// wave. ovf_buf holds ovf_slots record buffers of ovf_cap records, each owned
-// by the block that claimed its flag in ovf_flags (zero when free); null:
-// every overflowing hit is added at once.
-__global__ __launch_bounds__(kTraceBlock) void k_trace_backward(
-    const float *__restrict__ header, const float4 *__restrict__ nodes4, const float4 *__restrict__ rec, const float4 *__restrict__ origins,
-    const float *__restrict__ dirs, PoolMap pm, Cuts c, const float *__restrict__ grad_ray,
+// recover T_final (skipped when the forward's T are given), then again
+// with the same visits in the same order, recording dL/dalpha_j = -g T_final /
+// (1 - alpha_j) of each included, unclamped Gaussian. The source's own term
+// (through the ray origin) is summed over the ray.
+template <bool kOnePool, bool kChain>
+__global__ __launch_bounds__(kTraceBlock, kOnePool ? 4 : kStreamBlocksPerCu) void k_adjoint_trace(
+    const float *__restrict__ header, const float4 *__restrict__ nodes4, const float4 *__restrict__ rec, GridPools pools,
+    int64_t first, int64_t n_pools, Cuts c,
+    unsigned long long *__restrict__ queues, const float *__restrict__ grad_ray,
     const float *__restrict__ grad_mean_in, const float *__restrict__ vis_fwd, float *go, float *gm, float *gl,
-    float4 *ovf_buf, uint32_t *ovf_flags, int ovf_slots, int ovf_cap) {
-    __shared__ Pair stk[kPoolRing * kTraceBlock];
+    AdjScratch sc) {
+    __shared__ Pair stk[kStreamRing * kTraceBlock];
     __shared__ Pair fifo[kFifo * kTraceBlock];
-    __shared__ float ogr[kWavesPerBlock][64 * 3];   // origin terms per item
-    __shared__ GradTable table;
-    // the block's four items (64 Gaussians x a chunk of directions each),
-    // drained together: item sizes, their Gaussians and first directions
-    __shared__ int item_n[kWavesPerBlock], item_nv[kWavesPerBlock], item_k0[kWavesPerBlock];
-    __shared__ int64_t item_m0[kWavesPerBlock];
-    __shared__ int blk_next;
-    __shared__ int ovf_slot, ovf_n;   // the block's record buffer (-1: none) and its records
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (!tree_matches(header, pm.n)) {
+    __shared__ __align__(16) typename AdjStage<kChain>::Lds stage_lds[kWavesPerBlock];
+    const int64_t n = pools.m_hi;
+    if (!tree_matches(header, n)) {
         // a tree built for another Gaussian set: every gradient is NaN
         const float nan = __int_as_float(0x7fc00000);
-        for (int64_t j = (int64_t)blockIdx.x * kTraceBlock + threadIdx.x; j < pm.n;
-             j += (int64_t)gridDim.x * kTraceBlock) {
+        for (int64_t j = (int64_t)blockIdx.x * kTraceBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kTraceBlock) {
             go[j] = nan;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) gm[3 * j + c] = gl[3 * j + c] = nan;
+            for (int x = 0; x < 3; ++x) gm[3 * j + x] = gl[3 * j + x] = nan;
         }
         return;
     }
-    for (int s = threadIdx.x; s < kHashSlots; s += kTraceBlock) {
-        table.key[s] = -1;
-#pragma unroll
-        for (int c = 0; c < 7; ++c) table.val[c][s] = 0.0f;
-    }
-    if (threadIdx.x == 0) {
-        // claim a free record buffer: at most one pass over the flags, so a
-        // block never waits on another (without one, overflow goes out at once)
-        int got = -1;
-        if (ovf_buf) {
-            const int start = (int)(blockIdx.x % (unsigned)ovf_slots);
-            for (int i = 0; i < ovf_slots && got < 0; ++i) {
-                const int sl = start + i < ovf_slots ? start + i : start + i - ovf_slots;
-                if (atomicCAS(ovf_flags + sl, 0u, 1u) == 0u) got = sl;
-            }
-        }
-        ovf_slot = got;
-        ovf_n = 0;
-    }
-    // item wv: every wave reaches the barriers; items past the end are empty
-    int64_t w = pm.w_off + xcd_chunk_block<kAdjChunk>(blockIdx.x, gridDim.x) * kWavesPerBlock + wv;
-    const bool wave_live = w < pm.n_items;
-    if (!wave_live) w = 0;
-    const int64_t grp = w / pm.n_chunks;
-    const int chunk = (int)(w - grp * pm.n_chunks);
-    const int64_t my_m0 = grp * 64;
-    const int my_nv = (int)min<int64_t>(64, pm.n - my_m0);
-    const int K = pm.K;
-    if (lane == 0) {
-        item_n[wv] = wave_live ? my_nv * min(kPoolS, K - chunk * kPoolS) : 0;
-        item_nv[wv] = my_nv;
-        item_k0[wv] = chunk * kPoolS;
-        item_m0[wv] = my_m0;
-    }
-    if (threadIdx.x == 0) blk_next = 0;
-    ogr[wv][lane] = 0.f;
-    ogr[wv][64 + lane] = 0.f;
-    ogr[wv][128 + lane] = 0.f;
-    __syncthreads();
-    // block ray r: item it with n_0 + .. + n_(it-1) <= r, local index r - that sum
-    const int n_a = item_n[0], n_b = n_a + item_n[1], n_c = n_b + item_n[2], total = n_c + item_n[3];
-    GridSource src;
-    src.rec = rec;
-    src.origins = origins;
-    src.dirs = dirs;
-    src.dir_mode = c.dir_mode;
-    src.tmin_scale = c.tmin_scale;
-    src.K = K;
-
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint64_t lt = (1ull << lane) - 1ull;
-    Walk<kPoolRing> wk;
-    Pair spill[Walk<kPoolRing>::kSpill];
+    AdjStage<kChain> stage;
+    stage.s = stage_lds + wv;
+    stage.n = 0;
+    std::conditional_t<kOnePool, RangeQueue, XcdQueue> queue;
+    if constexpr (kOnePool) {
+        queue.next = first + xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + wv;
+        queue.end = min(n_pools, queue.next + 1);
+    } else {
+        queue.init(queues, n_pools, (int)(blockIdx.x % kXcds));
+    }
+
+    Walk<kStreamRing> wk;
+    Pair spill[Walk<kStreamRing>::kSpill];
     wk.init(stk + threadIdx.x, fifo + threadIdx.x, spill);
-    int oi = 0, it = 0;  // item and item origin of the current ray
-    float gk = 0.f;      // upstream gradient of the current ray
     RayBox rb;
     rb.set(mk(0.f, 0.f, 0.f), mk(0.f, 0.f, 0.f));
     f3 d = mk(0.f, 0.f, 0.f);
-    float tmin = 0.f, T = 1.f;
+    float tmin = 0.f, T = 1.f, gk = 0.f;   // gk: upstream gradient of the current ray
     int32_t self = -1, self_leaf_m1 = -2;
-    GradScatter gs;
+    GradRecord gs;
     gs.active = false;
+    gs.keep = sc.acc != nullptr;
     gs.g_over = 0.f;
+    gs.origin = mk(0.f, 0.f, 0.f);
     gs.go = go;
     gs.gm = gm;
     gs.gl = gl;
-    gs.table = &table;
-    gs.origin = mk(0.f, 0.f, 0.f);
-    gs.ovf = ovf_slot >= 0 ? ovf_buf + 2 * (int64_t)ovf_slot * ovf_cap : nullptr;
-    gs.ovf_n = &ovf_n;
-    gs.ovf_cap = ovf_cap;
-    bool drained = false;  // wave-uniform: the block's rays are all handed out
+    gs.a = 0.f;
+    gs.e = mk(0.f, 0.f, 0.f);
+    uint4 ahead[3] = {};   // kOnePool: the words of wk.node
+    auto node_words = [&](uint4 (&w)[3]) {
+        const uint4 *r = reinterpret_cast<const uint4 *>(nodes4) + 4 * (int64_t)wk.node + 4;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w[k] = r[k];
+    };
+    // wave-uniform pool state
+    int next = 0, pool_n = 0;
+    bool more = true;
 
     for (uint32_t round = 1;; ++round) {
-        const uint64_t need = __ballot(wk.idle());
-        if (need != 0 && !drained && (__popcll(need) >= kRefillMin || ~need == 0)) {
-            // the wave's first active lane reserves one block ray per idle lane
-            const int cnt = __popcll(need);
-            int base = 0;
-            if (lane == __builtin_amdgcn_readfirstlane(lane)) base = atomicAdd(&blk_next, cnt);
-            base = __builtin_amdgcn_readfirstlane(base);
-            if (base + cnt >= total) drained = true;
-            const int idx = base + __popcll(need & lt);
-            if (wk.idle() && idx < total) {
-                it = (idx >= n_a) + (idx >= n_b) + (idx >= n_c);
-                const int local = idx - (it == 0 ? 0 : it == 1 ? n_a : it == 2 ? n_b : n_c);
-                src.m0 = item_m0[it];
-                src.nv = item_nv[it];
-                src.inv_nv = __builtin_amdgcn_rcpf((float)src.nv);
-                src.k0 = item_k0[it];
-                const RaySetup r = src(local);
-                oi = (int)(r.self_leaf - src.m0);
+        uint64_t need = __ballot(wk.idle());
+        if (__popcll(need) < c.refill && ~need != 0) need = 0;
+        while (need != 0 && more) {
+            if (next >= pool_n) {
+                int64_t p;
+                more = queue.take(p);
+                pool_n = more ? pools.open(p) : 0;
+                next = 0;
+                continue;
+            }
+            const int idx = next + __popcll(need & lt);
+            if (wk.idle() && idx < pool_n) {
+                const RaySetup r = pools(idx);
                 // r.out = i K + k: the ray's place in grad_ray and vis_fwd
-                gk = (grad_mean_in ? grad_mean_in[r.self] / (float)K : 0.0f) + (grad_ray ? grad_ray[r.out] : 0.0f);
+                gk = (grad_mean_in ? grad_mean_in[r.self] / (float)pools.K : 0.0f) + (grad_ray ? grad_ray[r.out] : 0.0f);
                 d = r.d;
                 rb.set(r.o, d);
                 tmin = r.tmin;
@@ -876,99 +855,85 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_backward(
                 gs.active = vis_fwd != nullptr || gk == 0.0f;
                 gs.g_over = vis_fwd ? -gk * vis_fwd[r.out] : 0.0f;
                 T = 1.0f;
-                wk.start(pm.n, gk != 0.0f);
+                wk.start(n, gk != 0.0f);
+                if (kOnePool && wk.node > Walk<kStreamRing>::kDone) node_words(ahead);
             }
+            next += __popcll(need);
+            need = __ballot(wk.idle());
         }
         if (__ballot(!wk.idle()) == 0) break;
 
         if (wk.can_walk()) {
-            const uint4 *r = reinterpret_cast<const uint4 *>(nodes4) + 4 * (int64_t)wk.node + 4;
-            const uint4 w[3] = {r[0], r[1], r[2]};
-            wk.visit(w, rb, tmin, T);
+            if (kOnePool) {
+                wk.visit(ahead, rb, tmin, T);
+                if (wk.node > Walk<kStreamRing>::kDone) node_words(ahead);
+            } else {
+                uint4 w[3];
+                node_words(w);
+                wk.visit(w, rb, tmin, T);
+            }
         }
 
         if (leaf_phase_now(wk)) {
+            int32_t m1 = 0;
+            gs.hit = false;
             if (wk.queued()) {
-                const int32_t m1 = wk.next_leaf();
+                m1 = wk.next_leaf();
                 T *= leaf_factor(rec, m1, rb.o, d, tmin, self, self_leaf_m1, c, gs, T);
                 if (T < c.T_stop) wk.stop();
             }
+            stage.put(gs.hit, m1 + 1, gs.a, gs.e, sc);
         }
         if (round % kBudgetLook == 0 && wk.budget < 0 && !wk.idle()) {
             T = __int_as_float(0x7fc00000);
             wk.stop();
         }
 
-        if (wk.finished()) {
-            if (!gs.active) {
-                // T_final is known: trace the same ray again, scattering
-                gs.g_over = -gk * T;
-                gs.active = true;
-                T = 1.0f;
-                wk.start(pm.n, true);
-            } else {
-                if (gs.origin.x != 0.f || gs.origin.y != 0.f || gs.origin.z != 0.f) {
-                    atomicAdd(&ogr[it][3 * oi + 0], gs.origin.x);
-                    atomicAdd(&ogr[it][3 * oi + 1], gs.origin.y);
-                    atomicAdd(&ogr[it][3 * oi + 2], gs.origin.z);
-                }
-                wk.node = Walk<kPoolRing>::kIdle;
-            }
+        const bool finished = wk.finished();
+        if (__ballot(finished) == 0) continue;
+        const bool ended = finished && gs.active;
+        const bool moved = ended && (gs.origin.x != 0.f || gs.origin.y != 0.f || gs.origin.z != 0.f);
+        stage.put(moved && gs.keep, ~(self_leaf_m1 + 1), 0.f, gs.origin, sc);
+        if (moved && !gs.keep) {
+            unsafeAtomicAdd(gm + 3 * (int64_t)self + 0, gs.origin.x);
+            unsafeAtomicAdd(gm + 3 * (int64_t)self + 1, gs.origin.y);
+            unsafeAtomicAdd(gm + 3 * (int64_t)self + 2, gs.origin.z);
+        }
+        if (ended) wk.node = Walk<kStreamRing>::kIdle;
+        if (finished && !gs.active) {
+            // T_final is known: trace the same ray again, recording
+            gs.g_over = -gk * T;
+            gs.active = true;
+            T = 1.0f;
+            wk.start(n, true);
+            if (kOnePool && wk.node > Walk<kStreamRing>::kDone) node_words(ahead);
         }
     }
-    // every wave has finished: the origin sums of all items and the table
-    // are complete
-    __syncthreads();
-    if (wave_live && lane < my_nv) {
-        const float ox = ogr[wv][3 * lane], oy = ogr[wv][3 * lane + 1], oz = ogr[wv][3 * lane + 2];
-        if (ox != 0.f || oy != 0.f || oz != 0.f) {
-            const int64_t j = __float_as_int(rec[kLeafF4 * (my_m0 + lane) + 2].w);
-            unsafeAtomicAdd(gm + 3 * j + 0, ox);
-            unsafeAtomicAdd(gm + 3 * j + 1, oy);
-            unsafeAtomicAdd(gm + 3 * j + 2, oz);
-        }
-    }
-    // the block's table: one set of global atomics per Gaussian
-    auto flush_table = [&]() {
-        for (int s = threadIdx.x; s < kHashSlots; s += kTraceBlock) {
-            const int64_t j = table.key[s];
-            if (j < 0) continue;
-            const float v[7] = {table.val[0][s], table.val[1][s], table.val[2][s], table.val[3][s],
-                                table.val[4][s], table.val[5][s], table.val[6][s]};
-            add_grad_global(go, gm, gl, j, v);
-        }
-    };
-    flush_table();
-    if (ovf_slot < 0) return;   // block-uniform
-    // second pass: the hits that found no slot, summed per Gaussian in the
-    // emptied table (most of them now fit), then flushed once more
-    __syncthreads();
-    for (int s = threadIdx.x; s < kHashSlots; s += kTraceBlock) {
-        table.key[s] = -1;
+    stage.flush(sc);
+}
+
+// The caller's gradients from the accumulators: with S the sums of a, a e and
+// a e^2 over the hits of leaf m, dL/do = S_a / o, dL/dmu = W^T S_ae + the origin
+// terms, dL/dlog_scale = S_ae2.
+__global__ __launch_bounds__(256) void k_adjoint_add(const float *__restrict__ header, const float4 *__restrict__ rec,
+                                                     int64_t n, const float4 *__restrict__ acc,
+                                                     const float4 *__restrict__ org, float *go, float *gm, float *gl) {
+    const int64_t m = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (m >= n || !tree_matches(header, n)) return;
+    const float4 s = acc[2 * m], t = acc[2 * m + 1], o = org[m];
+    const float4 r0 = rec[kLeafF4 * m], r1 = rec[kLeafF4 * m + 1], r2 = rec[kLeafF4 * m + 2];
+    const f3 w0 = mk(r1.x, r1.y, r1.z), w1 = mk(r2.x, r2.y, r2.z), w2 = r1.w * cross(w0, w1);
+    const f3 mu = s.y * w0 + s.z * w1 + s.w * w2 + mk(o.x, o.y, o.z);
+    const float v[7] = {s.x != 0.f ? s.x / r0.w : 0.f, mu.x, mu.y, mu.z, t.x, t.y, t.z};
+    bool any = false;
 #pragma unroll
-        for (int c = 0; c < 7; ++c) table.val[c][s] = 0.0f;
-    }
-    __syncthreads();
-    const float4 *rec_ovf = ovf_buf + 2 * (int64_t)ovf_slot * ovf_cap;
-    const int n_rec = min(ovf_n, ovf_cap);
-    for (int r = threadIdx.x; r < n_rec; r += kTraceBlock) {
-        const float4 a = rec_ovf[2 * r], b = rec_ovf[2 * r + 1];
-        const int32_t j = __float_as_int(a.x);
-        const float v[7] = {a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        const int slot = table.find(j);
-        if (slot >= 0) {
-#pragma unroll
-            for (int c = 0; c < 7; ++c) atomicAdd(&table.val[c][slot], v[c]);
-        } else {
-            add_grad_global(go, gm, gl, j, v);
-        }
-    }
-    __syncthreads();
-    flush_table();
-    // every record has been read: hand the buffer back
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) atomicExch(ovf_flags + ovf_slot, 0u);
+    for (int c = 0; c < 7; ++c) any = any || v[c] != 0.f;
+    if (any) add_grad_global(go, gm, gl, __float_as_int(r2.w), v);
+}
+
+// Words [0, count) to v.
+__global__ __launch_bounds__(256) void k_fill_u32_wide(uint32_t *__restrict__ p, int64_t count, uint32_t v) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) p[i] = v;
 }
 
 __global__ __launch_bounds__(64) void k_fill_u32_trace(uint32_t *__restrict__ p, int64_t count, uint32_t v) {
@@ -1226,33 +1191,64 @@ extern "C" rv_status rv_trace_visibility_backward(const void *bvh, const rv_gaus
                "rv_trace_visibility_backward: both upstream gradients are NULL");
     RV_REQUIRE(grad_opacity && grad_mean && grad_log_scale, RV_ERR_INVALID_ARG,
                "rv_trace_visibility_backward: null gradient output");
-    const PoolMap pm = make_pool(g->n, K);
-    const BvhLayout L = bvh_layout(g->n);
-    const Cuts c = make_cuts(*p);
-    // record buffers of the blocks' second pass (stream-ordered, freed after
-    // the launches); without them every overflowing hit goes out at once
+    const int64_t n = g->n;
+    const BvhLayout L = bvh_layout(n);
+    Cuts c = make_cuts(*p);
+    c.refill = refill_lanes(n);
     hipStream_t s = (hipStream_t)stream;
-    const size_t flag_bytes = align_up((size_t)kOvfSlots * sizeof(uint32_t));
-    const size_t ovf_bytes = flag_bytes + (size_t)kOvfSlots * kOvfCap * 2 * sizeof(float4);
-    void *ovf_mem = nullptr;
-    if (hipMallocAsync(&ovf_mem, ovf_bytes, s) != hipSuccess) {
-        ovf_mem = nullptr;
+    GridPools pools;
+    pools.rec = at<float4>(bvh, L.leaf_rec);
+    pools.origins = at<float4>(bvh, L.origins);
+    pools.dirs = dirs;
+    pools.dir_mode = c.dir_mode;
+    pools.tmin_scale = c.tmin_scale;
+    pools.K = K;
+    pools.m0 = 0;
+    pools.nv = 1;
+    pools.k0 = 0;
+    pools.inv_nv = 1.0f;
+    pools.m_hi = n;
+    pools.n_chunks = (K + kStreamPoolS - 1) / kStreamPoolS;
+    const int64_t n_pools = ((n + 63) / 64) * (int64_t)pools.n_chunks;
+    // accumulators (stream-ordered, freed after the launches); without them every
+    // term goes to the caller's arrays at once
+    AdjScratch sc{};
+    unsigned long long *queues = nullptr;
+    const size_t off_acc = kQueueBytes, off_org = off_acc + (size_t)n * 8 * sizeof(float);
+    const size_t bytes = off_org + (size_t)n * 4 * sizeof(float);
+    void *mem = nullptr;
+    if (hipMallocAsync(&mem, bytes, s) != hipSuccess) {
+        mem = nullptr;
         (void)hipGetLastError();
     }
-    uint32_t *ovf_flags = static_cast<uint32_t *>(ovf_mem);
-    float4 *ovf_buf = ovf_mem ? reinterpret_cast<float4 *>(static_cast<char *>(ovf_mem) + flag_bytes) : nullptr;
-    if (ovf_mem) hipLaunchKernelGGL(k_fill_u32_trace, dim3(1), dim3(64), 0, s, ovf_flags, (int64_t)kOvfSlots, 0u);
-    for (int64_t w0 = 0; w0 < pm.n_items; w0 += kLaunchWaves) {
-        PoolMap part = pm;
-        part.w_off = w0;
-        const int64_t nb = (std::min(kLaunchWaves, pm.n_items - w0) + kWavesPerBlock - 1) / kWavesPerBlock;
-        hipLaunchKernelGGL(k_trace_backward, dim3((unsigned)nb), dim3(kTraceBlock), 0, s,
-                           at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), at<float4>(bvh, L.origins), dirs,
-                           part, c, grad_vis_ray, grad_vis_mean, vis_ray_fwd, grad_opacity, grad_mean, grad_log_scale,
-                           ovf_buf, ovf_flags, kOvfSlots, kOvfCap);
+    if (mem) {
+        queues = at<unsigned long long>(mem, 0);
+        sc.acc = at<float>(mem, off_acc);
+        sc.org = at<float>(mem, off_org);
+        const int64_t words = (int64_t)(bytes / sizeof(uint32_t));
+        hipLaunchKernelGGL(k_fill_u32_wide, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0, s,
+                           static_cast<uint32_t *>(mem), words, 0u);
     }
+    if (mem && n_pools > kAdjOnePoolWaves) {
+        const auto kernel = n_pools > kFewPools ? k_adjoint_trace<false, true> : k_adjoint_trace<false, false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)stream_blocks(n_pools, n)), dim3(kTraceBlock), 0, s,
+                           at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), pools,
+                           int64_t(0), n_pools, c, queues, grad_vis_ray, grad_vis_mean, vis_ray_fwd, grad_opacity,
+                           grad_mean, grad_log_scale, sc);
+    } else {
+        for (int64_t first = 0; first < n_pools; first += kLaunchWaves)
+            hipLaunchKernelGGL((k_adjoint_trace<true, false>),
+                               dim3(grid_for(std::min(kLaunchWaves, n_pools - first), kWavesPerBlock)),
+                               dim3(kTraceBlock), 0, s, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4),
+                               at<float4>(bvh, L.leaf_rec), pools, first, n_pools, c, queues, grad_vis_ray, grad_vis_mean,
+                               vis_ray_fwd, grad_opacity, grad_mean, grad_log_scale, sc);
+    }
+    if (mem)
+        hipLaunchKernelGGL(k_adjoint_add, dim3(grid_for(n, 256)), dim3(256), 0, s, at<float>(bvh, L.header),
+                           at<float4>(bvh, L.leaf_rec), n, reinterpret_cast<const float4 *>(sc.acc),
+                           reinterpret_cast<const float4 *>(sc.org), grad_opacity, grad_mean, grad_log_scale);
     const rv_status st_launch = check_launch("rv_trace_visibility_backward");
-    if (ovf_mem) (void)hipFreeAsync(ovf_mem, s);
+    if (mem) (void)hipFreeAsync(mem, s);
     return st_launch;
 }
 
