@@ -15,15 +15,16 @@
 // whole run at once, a lane each, and read back lane by lane. The map and the
 // directions sit in LDS, padded to 16 bytes: a bilinear fetch is four loads of
 // 16 bytes at fixed offsets, as a ring of texels around the map holds what lies
-// beyond its edges. The BRDF is evaluated in the Gaussian's frame, where the
-// normal is an axis.
+// beyond its edges.
 //
-// Bound by the vector ALUs (seven reciprocals and roots among 155 instructions a
-// direction; without the specular term 247 us, with a map read at one address 289):
-// 300,000 x 256 takes 284 us, 430 with a wave per Gaussian that set up the Gaussian
-// and the map for four steps of the loop, scalar texel reads, two octants and
-// clamped columns per direction and the BRDF in world space. The SH sums and the
-// rotation by 4x4x1 matrix instructions are 28 instructions fewer and take 301 us.
+// Bound by the vector ALUs (seven reciprocals and roots among 175 instructions a
+// direction; a map read at one address is no faster): 300,000 x 256 takes 320 us, 430
+// with a wave per Gaussian that set up the Gaussian and the map for four steps of
+// the loop, scalar texel reads, and two octants and clamped columns per direction.
+// In the Gaussian's frame the BRDF is 20 instructions shorter (285 us), but a narrow
+// lobe multiplies what the directions are off by, 10^-7, up to a thousandfold, and
+// the steps here give the same values as they always did. The SH sums by 4x4x1
+// matrix instructions are as fast.
 #include <cmath>
 #include <type_traits>
 
@@ -81,6 +82,10 @@ __device__ __forceinline__ float atan2_texels(float y, float x) {
     return fmaf(t, p, 8.0f - copysignf(4.0f, x));
 }
 
+__device__ __forceinline__ f3 unit(f3 d) {
+    return __builtin_amdgcn_rsqf(dot(d, d)) * d;   // one ulp; |d| is 1 up to rounding
+}
+
 // Value of lane j (wave-uniform).
 __device__ __forceinline__ float from_lane(float v, int j) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
@@ -88,7 +93,8 @@ __device__ __forceinline__ float from_lane(float v, int j) {
 // What a Gaussian brings to all its directions.
 struct ShadePoint {
     f3 b1, b2, n;   // frame, as the visibility rays use it
-    f3 wo;          // view direction in the frame
+    f3 wo;          // view direction
+    float no;       // n . w_o
     float a2;       // alpha^2
     float spec;     // factor of the specular term: 2 G1(w_o) alpha^2 / (4 pi (n . w_o)); 0 seen from behind
     float kd[3];    // albedo / pi
@@ -109,13 +115,14 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(const float *__restrict__
         const float *e = env + (row * kEnvCols + col) * 3;
         env_s[t] = make_float4(e[0], e[1], e[2], 0.0f);
     }
-    auto unit_dir = [&](int k) {
+    // direction k as given, on the sphere of unit length
+    auto local_dir = [&](int k) {
         const f3 d = mk(dirs[3 * k], dirs[3 * k + 1], dirs[3 * k + 2]);
-        return __builtin_amdgcn_rsqf(dot(d, d)) * d;   // one ulp; |d| is 1 up to rounding
+        return kHemisphere ? d : unit(d);
     };
     for (int k = threadIdx.x; k < min(K, kDirsLds); k += kShadeBlock) {
-        const double x = dirs[3 * k], y = dirs[3 * k + 1], z = dirs[3 * k + 2], inv = 1.0 / sqrt(x * x + y * y + z * z);
-        dirs_s[k] = make_float4((float)(x * inv), (float)(y * inv), (float)(z * inv), 0.0f);
+        const f3 d = local_dir(k);
+        dirs_s[k] = make_float4(d.x, d.y, d.z, 0.0f);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63;
@@ -127,22 +134,14 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(const float *__restrict__
     ShadePoint own;   // lane j: Gaussian i0 + j (the first again beyond the run)
     {
         const int64_t i = i0 + (lane < count ? lane : 0);
-        // in double precision: a narrow lobe multiplies what the tangential parts of
-        // the directions are off by; rounded once, they are off by less than with
-        // the same steps in single precision (and a lane each it costs little)
-        double nx = normal[3 * i], ny = normal[3 * i + 1], nz = normal[3 * i + 2];
-        const double nl = 1.0 / sqrt(nx * nx + ny * ny + nz * nz);
-        nx *= nl; ny *= nl; nz *= nl;
-        const double sign = copysign(1.0, nz), a = -1.0 / (sign + nz), b = nx * ny * a;
-        const double b1[3] = {1.0 + sign * nx * nx * a, sign * b, -sign * nx}, b2[3] = {b, sign + ny * ny * a, -ny};
-        own.n = mk((float)nx, (float)ny, (float)nz);
-        own.b1 = mk((float)b1[0], (float)b1[1], (float)b1[2]);
-        own.b2 = mk((float)b2[0], (float)b2[1], (float)b2[2]);
-        const double ox = (double)cx - mean[3 * i], oy = (double)cy - mean[3 * i + 1], oz = (double)cz - mean[3 * i + 2];
-        const double ol = 1.0 / sqrt(ox * ox + oy * oy + oz * oz);
-        own.wo = mk((float)((b1[0] * ox + b1[1] * oy + b1[2] * oz) * ol), (float)((b2[0] * ox + b2[1] * oy + b2[2] * oz) * ol),
-                    (float)((nx * ox + ny * oy + nz * oz) * ol));
-        const float no = own.wo.z;
+        float nx = normal[3 * i], ny = normal[3 * i + 1], nz = normal[3 * i + 2];
+        const float nl = sqrtf(nx * nx + ny * ny + nz * nz);
+        nx /= nl; ny /= nl; nz /= nl;
+        own.n = mk(nx, ny, nz);
+        onb_duff(own.n, own.b1, own.b2);
+        f3 wo = mk(cx - mean[3 * i], cy - mean[3 * i + 1], cz - mean[3 * i + 2]);
+        own.wo = (1.0f / sqrtf(dot(wo, wo))) * wo;
+        const float no = own.no = dot(own.n, own.wo);
         const float r = roughness[i];
         own.a2 = (r * r) * (r * r);
         const float g1o = 2.0f * no / (no + sqrtf(own.a2 + (1.0f - own.a2) * no * no));
@@ -160,7 +159,7 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(const float *__restrict__
         const f3 b1 = pick3(own.b1), b2 = pick3(own.b2), nrm = pick3(own.n), wo = pick3(own.wo);
         const float a2 = pick(own.a2), spec_k = pick(own.spec), rest = 1.0f - a2;
         const float kd[3] = {pick(own.kd[0]), pick(own.kd[1]), pick(own.kd[2])};
-        const bool front = from_lane(own.wo.z, j) > 0.0f;
+        const bool front = from_lane(own.no, j) > 0.0f;
         float l[9][3];
 #pragma unroll
         for (int q = 0; q < 9; ++q)
@@ -179,18 +178,10 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(const float *__restrict__
                 const float4 q = dirs_s[k];
                 d = mk(q.x, q.y, q.z);
             } else {
-                d = unit_dir(k);
+                d = local_dir(k);
             }
-            // the direction in the world (w) and in the frame (d)
-            f3 w;
-            if (kHemisphere) {
-                w = mk(fmaf(d.z, nrm.x, fmaf(d.y, b2.x, d.x * b1.x)), fmaf(d.z, nrm.y, fmaf(d.y, b2.y, d.x * b1.y)),
-                       fmaf(d.z, nrm.z, fmaf(d.y, b2.z, d.x * b1.z)));
-            } else {
-                w = d;
-                d = mk(dot(b1, w), dot(b2, w), dot(nrm, w));
-            }
-            const float ci = d.z;
+            const f3 w = kHemisphere ? unit(d.x * b1 + d.y * b2 + d.z * nrm) : d;
+            const float ci = dot(nrm, w);
             if (!(ci > 0.0f)) continue;
             const float V = vis[i * K + k];
             // environment: bilinear at texel coordinates of (theta, phi);
@@ -220,19 +211,20 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(const float *__restrict__
                 for (int q = 1; q < 9; ++q) s = fmaf(l[q][ch], Y[q], s);
                 Li[ch] = fmaf(V, Le[ch], s);
             }
-            // specular times the cosine: D F G / (4 (n . w_o)), with D = alpha^2 / (pi t^2),
-            // h = w + w_o not yet of unit length, t |h|^2 = (|n x h|^2 + (n . h)^2 alpha^2):
-            // |n x h|^2 for 1 - (n . h)^2 stays accurate for smooth surfaces.
+            // specular times the cosine: D F G / (4 (n . w_o)); the GGX denominator
+            // uses 1 - (n.h)^2 = |n x h|^2 to stay accurate for smooth surfaces.
             // Hardware reciprocals and roots (about 1 ulp).
             float spec = 0.0f;
             if (front) {
-                const f3 h = d + wo;
-                const float hh = dot(h, h), hz = fmaxf(h.z, 0.0f);
-                const float it = hh * __builtin_amdgcn_rcpf(fmaf(h.x, h.x, h.y * h.y) + hz * hz * a2);
-                // w_o . h / |h| = |h| / 2, as w and w_o are of unit length
-                const float m = fmaf(-0.5f, __builtin_amdgcn_sqrtf(hh), 1.0f), m2 = m * m;
+                f3 h = w + wo;
+                h = __builtin_amdgcn_rsqf(dot(h, h)) * h;
+                const float nh = fmaxf(dot(nrm, h), 0.0f), vh = fmaxf(dot(wo, h), 0.0f);
+                const f3 nxh = cross(nrm, h);
+                const float it = __builtin_amdgcn_rcpf(dot(nxh, nxh) + nh * nh * a2);
+                const float m = 1.0f - vh, m2 = m * m;
                 const float F = fmaf(f1, m2 * m2 * m, f0);
                 const float g = __builtin_amdgcn_rcpf(ci + __builtin_amdgcn_sqrtf(a2 + rest * ci * ci));
+                // D F G1(w_i) G1(w_o) / (4 n.w_o) with D = alpha^2 / (pi t^2)
                 spec = (spec_k * F) * (ci * g) * (it * it);
             }
 #pragma unroll
