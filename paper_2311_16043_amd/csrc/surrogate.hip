@@ -114,7 +114,7 @@ __device__ __forceinline__ float enc_feature(int f, float u0, float u1, float u2
 
 // ---- forward -----------------------------------------------------------------------
 
-enum FwdMode { kModeXd = 0, kModeGrid = 1, kModeTrain = 2 };
+enum FwdMode { kModeXd = 0, kModeGrid = 1 };
 
 struct FwdArgs {
     const float *master;
@@ -144,14 +144,13 @@ struct FwdArgs {
 };
 
 // Training takes the batch in blocks of kTrainNT 16-sample tiles, each block
-// kTrainWaves waves that split every layer's outputs (kTrainOps k-blocks of
-// the next layer's input per wave), and covers the batch rounded up to 32
+// kTrainWaves waves that split every layer's outputs (a k-block of the next
+// layer's input per wave), and covers the batch rounded up to 32
 // samples: the padded samples' activations and gradients are stored as zeros
 // for the weight-gradient products, which step over 32 samples at a time.
 constexpr int kTrainWaves = 8, kTrainNT = 2;
-constexpr int kTrainOps = 8 / kTrainWaves;
 constexpr int64_t kTrainPad = 16 * kTrainNT > 32 ? 16 * kTrainNT : 32;
-static_assert(kTrainWaves * kTrainOps == 8 && kTrainPad % (16 * kTrainNT) == 0 && kTrainPad <= 128,
+static_assert(kTrainWaves == 8 && kTrainPad % (16 * kTrainNT) == 0 && kTrainPad <= 128,
               "training block shape");
 __host__ __device__ constexpr int64_t train_pad(int64_t n) { return ((n + kTrainPad - 1) / kTrainPad) * kTrainPad; }
 
@@ -161,38 +160,28 @@ constexpr int64_t kHtRows = 64 + 4 * 256;
 constexpr int64_t kDzRows = 4 * 256 + 16;  // dZ1..dZ4 (256 rows each), dZ5 (2 rows, 16 reserved)
 __host__ __device__ constexpr int64_t dz_row(int l) { return l < 4 ? (int64_t)l * 256 : 1024; }  // l = 0..4
 
-// Output blocks 2 op and 2 op + 1 of a hidden layer for NT 16-sample tiles:
-// act (B operands, k-blocks of the input) -> the ReLU outputs as k-block op of
-// the next layer's B operand (bias in FP32, one v_cvt_pk_bf16_f32 per pair, then the ReLU
-// on the packed word).
+// Output blocks 2 op and 2 op + 1 of a layer (KB k-blocks of inputs): their packed
+// weights, block h and k-block kb in f[2 kb + h], and the products with act.
+template <int KB>
+__device__ __forceinline__ void load_pair(const u32x4 *__restrict__ A, int op, int lane, u32x4 (&f)[16]) {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) f[2 * kb + h] = A[((2 * op + h) * KB + kb) * 64 + lane];
+}
 template <int KB, int NT>
-__device__ __forceinline__ void fwd_pair(const u32x4 *__restrict__ A, const float *__restrict__ bias,
-                                         const u32x4 (&act)[8][NT], int op, int lane, u32x4 (&out)[NT]) {
-    const int g = lane >> 4;
-    f32x4 acc[2][NT];
+__device__ __forceinline__ void multiply_pair(const u32x4 (&f)[16], const u32x4 (&act)[8][NT], f32x4 (&acc)[2][NT]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[h][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-        const u32x4 a0 = A[((2 * op) * KB + kb) * 64 + lane];
-        const u32x4 a1 = A[((2 * op + 1) * KB + kb) * 64 + lane];
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            acc[0][nt] = mfma16(a0, act[kb][nt], acc[0][nt]);
-            acc[1][nt] = mfma16(a1, act[kb][nt], acc[1][nt]);
+            acc[0][nt] = mfma16(f[2 * kb], act[kb][nt], acc[0][nt]);
+            acc[1][nt] = mfma16(f[2 * kb + 1], act[kb][nt], acc[1][nt]);
         }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const float4 bv = *reinterpret_cast<const float4 *>(bias + (2 * op + h) * 16 + 4 * g);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            out[nt][2 * h + 0] = relu_bf16x2(pack2(acc[h][nt][0] + bv.x, acc[h][nt][1] + bv.y));
-            out[nt][2 * h + 1] = relu_bf16x2(pack2(acc[h][nt][2] + bv.z, acc[h][nt][3] + bv.w));
-        }
-    }
 }
 
 // The word of the lane next to this one (lanes 2c and 2c+1 swap): one DPP
@@ -226,20 +215,19 @@ __device__ __forceinline__ void store_kblock(uint16_t *__restrict__ ht, int64_t 
     }
 }
 
+// x mapped from [lo, hi] to [-1, 1].
+__device__ __forceinline__ float to_box(float x, float lo, float hi) {
+    const float span = hi - lo;
+    return span > 0.f ? 2.0f * (x - lo) / span - 1.0f : 0.0f;
+}
+
 // The encoded inputs of NT tiles of 16 samples from s_base as B operands
-// (k-blocks 0 and 1 of act; features kfeat), and the targets in training.
-// Every wave of a training block encodes its block's tiles itself.
+// (k-blocks 0 and 1 of act; features kfeat).
 template <int kMode, int NT>
-__device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, int lane, u32x4 (&act)[8][NT],
-                                             float (&Tv)[NT]) {
+__device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, int lane, u32x4 (&act)[8][NT]) {
     const int g = lane >> 4, col = lane & 15;
     const float lo0 = a.header[0], lo1 = a.header[1], lo2 = a.header[2];
     const float hi0 = a.header[3], hi1 = a.header[4], hi2 = a.header[5];
-    auto nrm = [](float x, float lo, float hi) {
-        const float span = hi - lo;
-        return span > 0.f ? 2.0f * (x - lo) / span - 1.0f : 0.0f;
-    };
-
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int64_t s = s_base + nt * 16 + col;
@@ -278,16 +266,11 @@ __device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, i
                 x0 = a.gmean[3 * i]; x1 = a.gmean[3 * i + 1]; x2 = a.gmean[3 * i + 2];
                 d0 = dv.x; d1 = dv.y; d2 = dv.z;
             } else {
-                int64_t idx = s;
-                if (kMode == kModeTrain && a.hashed)
-                    idx = (int64_t)(splitmix64(a.seed ^ splitmix64((uint64_t)a.step * 0x100000000ull + (uint64_t)s)) %
-                                    (uint64_t)a.n_samples);
-                x0 = a.x[3 * idx]; x1 = a.x[3 * idx + 1]; x2 = a.x[3 * idx + 2];
-                d0 = a.d[3 * idx]; d1 = a.d[3 * idx + 1]; d2 = a.d[3 * idx + 2];
-                if (kMode == kModeTrain) Tv[nt] = a.T[idx];
+                x0 = a.x[3 * s]; x1 = a.x[3 * s + 1]; x2 = a.x[3 * s + 2];
+                d0 = a.d[3 * s]; d1 = a.d[3 * s + 1]; d2 = a.d[3 * s + 2];
             }
         }
-        const float u0 = nrm(x0, lo0, hi0), u1 = nrm(x1, lo1, hi1), u2 = nrm(x2, lo2, hi2);
+        const float u0 = to_box(x0, lo0, hi0), u1 = to_box(x1, lo1, hi1), u2 = to_box(x2, lo2, hi2);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -297,67 +280,135 @@ __device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, i
     }
 }
 
-// Training forward: one block of kTrainWaves waves per kTrainNT 16-sample
-// tiles. Of every hidden layer's 16 output blocks (8 k-blocks of the next
-// layer's input), wave w produces k-blocks kTrainOps w .. kTrainOps (w + 1) - 1
-// and stores them as feature-major rows; the waves exchange each layer's
-// output through LDS (double-buffered, one barrier per layer). Wave 0
-// evaluates the head and the loss.
-__global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_forward_train(FwdArgs a) {
+// One block of eight waves takes two 16-sample tiles of the batch through the
+// network and back. Of every hidden layer's 16 output blocks (8 k-blocks of the
+// next layer's input) wave w produces k-block w, and of every input gradient
+// likewise; the waves exchange each layer's result through LDS (double-buffered, one
+// barrier per layer). Activations and gradients leave as feature-major rows for the
+// weight gradients; the ReLU masks stay in the registers of the wave that made
+// them. The head and its gradient are every wave's own.
+//
+// A block reads all 830 KB of packed weights, and with one block per CU (8,192
+// samples) that and the latency between its layers are the bound: a layer's weights
+// are fetched before the barrier that its inputs wait for. 22.5 us at 8,192 samples,
+// against 18.9 + 20.6 us as two kernels that fetched weights after the barrier, read
+// the masks back from memory and encoded every sample in all eight waves.
+__global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_train(FwdArgs a, const u32x4 *__restrict__ bwd,
+                                                                                 uint16_t *__restrict__ dz) {
     constexpr int NT = kTrainNT;
+    static_assert(kTrainWaves == 8 && NT == 2, "the encoding is split over the waves");
     __shared__ u32x4 xb[2][8][NT][64];
+    __shared__ float target[16 * NT];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t tile = blockIdx.x;
     const int64_t s_base = tile * (16 * NT);
     if (s_base >= train_pad(a.n)) return;  // block-uniform
     const int g = lane >> 4, col = lane & 15;
-    u32x4 act[8][NT];
-    float Tv[NT] = {};
-    encode_tiles<kModeTrain, NT>(a, s_base, lane, act, Tv);
+    const float *master = a.master;
+    u32x4 f[16], act[8][NT];   // weights and inputs of a layer
+    uint64_t relu = 0;         // the wave's outputs above zero, 16 bits a hidden layer
+    f32x4 acc[2][NT];
+    load_pair<2>(a.fwd + fwd_off(0) / 8, w, lane, f);
+
+    // encode: wave w words 2 (w / 4), 2 (w / 4) + 1 of k-block w % 2 of tile (w / 2) % 2
+    {
+        const int nt = (w >> 1) & 1, kb = w & 1, w0 = 2 * (w >> 2);
+        const int64_t s = s_base + nt * 16 + col;
+        float x0 = 0.f, x1 = 0.f, x2 = 0.f, d0 = 0.f, d1 = 0.f, d2 = 1.f, T = 0.f;
+        if (s < a.n) {
+            int64_t idx = s;
+            if (a.hashed)
+                idx = (int64_t)(splitmix64(a.seed ^ splitmix64((uint64_t)a.step * 0x100000000ull + (uint64_t)s)) %
+                                (uint64_t)a.n_samples);
+            x0 = a.x[3 * idx]; x1 = a.x[3 * idx + 1]; x2 = a.x[3 * idx + 2];
+            d0 = a.d[3 * idx]; d1 = a.d[3 * idx + 1]; d2 = a.d[3 * idx + 2];
+            T = a.T[idx];
+        }
+        const float u0 = to_box(x0, a.header[0], a.header[3]), u1 = to_box(x1, a.header[1], a.header[4]),
+                    u2 = to_box(x2, a.header[2], a.header[5]);
+        uint32_t *const out = reinterpret_cast<uint32_t *>(&xb[1][kb][nt][lane]) + w0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            out[q] = pack2(enc_feature(kfeat(kb, g, 2 * (w0 + q)), u0, u1, u2, d0, d1, d2),
+                           enc_feature(kfeat(kb, g, 2 * (w0 + q) + 1), u0, u1, u2, d0, d1, d2));
+        if (kb == 0 && w0 == 0 && g == 0) target[nt * 16 + col] = T;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) act[kb][nt] = xb[1][kb][nt][lane];
     if (w < 2) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            store_kblock(a.ht + ht_row(0) * a.stride, a.stride, w == 0 ? act[0][nt] : act[1][nt], w, lane,
-                         s_base + 16 * nt, a.n);
+            store_kblock(a.ht + ht_row(0) * a.stride, a.stride, xb[1][w][nt][lane], w, lane, s_base + 16 * nt,
+                         a.n);
     }
-    const float *master = a.master;
+
+    // the rest of hidden layer l, its products in acc: the wave's k-block for all
+    // waves and the next layer's inputs. Loops over layers stay rolled: each
+    // instruction is run once or thrice a block, and fetching it counts.
+    auto bias_of = [&](int l, float4 (&bv)[2]) {
 #pragma unroll
-    for (int l = 0; l < 4; ++l) {
-        const u32x4 *A = a.fwd + fwd_off(l) / 8;
-        uint16_t *ht = a.ht + ht_row(l + 1) * a.stride;
+        for (int h = 0; h < 2; ++h)
+            bv[h] = *reinterpret_cast<const float4 *>(master + off_b(l) + (2 * w + h) * 16 + 4 * g);
+    };
+    auto exchange = [&](const u32x4 (&o)[NT], int buf) {
 #pragma unroll
-        for (int q = 0; q < kTrainOps; ++q) {
-            const int op = kTrainOps * w + q;
-            u32x4 o[NT];
-            if (l == 0)
-                fwd_pair<2, NT>(A, master + off_b(0), act, op, lane, o);
-            else
-                fwd_pair<8, NT>(A, master + off_b(l), act, op, lane, o);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                store_kblock(ht, a.stride, o[nt], op, lane, s_base + 16 * nt, a.n);
-                xb[l & 1][op][nt][lane] = o[nt];
-            }
-        }
+        for (int nt = 0; nt < NT; ++nt) xb[buf][w][nt][lane] = o[nt];
         __syncthreads();
 #pragma unroll
         for (int kb = 0; kb < 8; ++kb)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) act[kb][nt] = xb[l & 1][kb][nt][lane];
+            for (int nt = 0; nt < NT; ++nt) act[kb][nt] = xb[buf][kb][nt][lane];
+    };
+    auto finish = [&](int l, const float4 (&bv)[2]) {
+        // bias in FP32, one v_cvt_pk_bf16_f32 per pair, then the ReLU on the packed word
+        u32x4 o[NT];
+        uint32_t bits = 0;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int h = q >> 1, r = 2 * (q & 1);
+                const uint32_t v = relu_bf16x2(pack2(acc[h][nt][r] + (r ? bv[h].z : bv[h].x),
+                                                     acc[h][nt][r + 1] + (r ? bv[h].w : bv[h].y)));
+                o[nt][q] = v;
+                bits |= ((v & 0xffffu) != 0u ? 1u : 0u) << (8 * nt + 2 * q) | ((v >> 16) != 0u ? 2u : 0u) << (8 * nt + 2 * q);
+            }
+        relu |= (uint64_t)bits << (16 * l);
+        exchange(o, l & 1);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            store_kblock(a.ht + ht_row(l + 1) * a.stride, a.stride, o[nt], w, lane, s_base + 16 * nt, a.n);
+    };
+    float4 bv[2];
+    bias_of(0, bv);
+    multiply_pair<2, NT>(f, act, acc);
+    load_pair<8>(a.fwd + fwd_off(1) / 8, w, lane, f);
+    finish(0, bv);
+#pragma unroll 1
+    for (int l = 1; l < 4; ++l) {
+        bias_of(l, bv);
+        multiply_pair<8, NT>(f, act, acc);
+        if (l < 3) {
+            load_pair<8>(a.fwd + fwd_off(l + 1) / 8, w, lane, f);
+        } else {
+#pragma unroll
+            for (int kb = 0; kb < 8; ++kb) f[kb] = a.fwd[fwd_off(4) / 8 + kb * 64 + lane];
+        }
+        finish(l, bv);
     }
-    if (w != 0) return;
 
     // head: one block of 16 outputs, rows 0 and 1 are z0, z1
     f32x4 acc5[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc5[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const u32x4 *A5 = a.fwd + fwd_off(4) / 8;
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) {
-        const u32x4 av = A5[kb * 64 + lane];
+    for (int kb = 0; kb < 8; ++kb)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc5[nt] = mfma16(av, act[kb][nt], acc5[nt]);
-    }
+        for (int nt = 0; nt < NT; ++nt) acc5[nt] = mfma16(f[kb], act[kb][nt], acc5[nt]);
+    load_pair<1>(bwd + bwd_off(0) / 8, w, lane, f);
     const float b50 = master[off_b(4)], b51 = master[off_b(4) + 1];
     const float inv_n = 1.0f / (float)a.n;
     float lsum = 0.f;
@@ -368,22 +419,55 @@ __global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_forw
         const float z0 = acc5[nt][0] + b50, z1 = acc5[nt][1] + b51;
         const float V = 1.0f / (1.0f + expf(-z0));
         const float U = z1;   // predicted |T - V|, linear (no saturating activation)
-        const float T = Tv[nt];
+        const float T = target[16 * nt + col];
         const float e = fabsf(T - V);
-        const float dz0 = (V - T) * inv_n;
         // squared error of U against |T - V| (V held constant)
-        const float dz1 = 2.0f * (U - e) * inv_n;
-        if (g == 0) {
-            a.dz5[s] = valid ? (uint16_t)bf16_bits(dz0) : (uint16_t)0;
-            a.dz5[a.stride + s] = valid ? (uint16_t)bf16_bits(dz1) : (uint16_t)0;
+        const uint32_t dz0 = valid ? bf16_bits((V - T) * inv_n) : 0u;
+        const uint32_t dz1 = valid ? bf16_bits(2.0f * (U - e) * inv_n) : 0u;
+        // as a B operand: outputs 0 and 1 sit in slots 0, 1 of lane group 0
+        act[0][nt] = u32x4{g == 0 ? (dz0 & 0xffffu) | (dz1 << 16) : 0u, 0u, 0u, 0u};
+        if (w == 0 && g == 0) {
+            a.dz5[s] = (uint16_t)dz0;
+            a.dz5[a.stride + s] = (uint16_t)dz1;
             if (valid) {
                 const float bce = -(T * logf(fmaxf(V, 1e-12f)) + (1.f - T) * logf(fmaxf(1.f - V, 1e-12f)));
                 lsum += bce + (U - e) * (U - e);
             }
         }
     }
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-    if (lane == 0) a.loss_part[tile] = lsum;
+    if (w == 0) {
+        for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+        if (lane == 0) a.loss_part[tile] = lsum;
+    }
+
+    // back: j = 0 through W5 (gradient dZ4), .., j = 3 through W2 (dZ1)
+    auto back = [&](int j) {
+        u32x4 o[NT];
+        const uint32_t bits = (uint32_t)(relu >> (16 * (3 - j)));
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            // the ReLU mask of the layer's input; none of a padded sample
+            const uint32_t m = s_base + 16 * nt + col < a.n ? bits >> (8 * nt) : 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int h = q >> 1, r = 2 * (q & 1);
+                o[nt][q] = pack2((m >> (2 * q)) & 1u ? acc[h][nt][r] : 0.0f, (m >> (2 * q)) & 2u ? acc[h][nt][r + 1] : 0.0f);
+            }
+        }
+        if (j < 3) exchange(o, j & 1);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            store_kblock(dz + dz_row(3 - j) * a.stride, a.stride, o[nt], w, lane, s_base + 16 * nt, a.n);
+    };
+    multiply_pair<1, NT>(f, act, acc);
+    load_pair<8>(bwd + bwd_off(1) / 8, w, lane, f);
+    back(0);
+#pragma unroll 1
+    for (int j = 1; j < 4; ++j) {
+        multiply_pair<8, NT>(f, act, acc);
+        if (j < 3) load_pair<8>(bwd + bwd_off(j + 1) / 8, w, lane, f);
+        back(j);
+    }
 }
 
 // ---- inference with the weights staged through LDS ------------------------------
@@ -503,8 +587,7 @@ __global__ __launch_bounds__(kInferWaves * 64, 1) void k_mlp_forward(FwdArgs a) 
     const float *master = a.master;
     load_chunk(F + fwd_off(0) / 8, 2048, wbuf[0], wv, lane);
     u32x4 act[8][NT];
-    float Tv[NT] = {};
-    encode_tiles<kMode, NT>(a, s_base, lane, act, Tv);
+    encode_tiles<kMode, NT>(a, s_base, lane, act);
     chunk_barrier();
     // layer 1 (64 -> 256) from buffer 0; layer 2's first half loads into buffer 1
     load_chunk(F + fwd_off(1) / 8, kChunkVec, wbuf[1], wv, lane);
@@ -554,128 +637,18 @@ __global__ __launch_bounds__(kInferWaves * 64, 1) void k_mlp_forward(FwdArgs a) 
     }
 }
 
-// ---- backward through the layers ----------------------------------------------
-
-// Output blocks 2 op and 2 op + 1 of dH = W dZ for NT 16-sample tiles (A =
-// the layer's backward operands, KB k-blocks of the output gradient in act),
-// masked by the ReLU of the layer's input (feature-major rows ht_in): the
-// pre-activation gradient of the layer below, stored as feature-major rows of
-// dz_out and returned as k-block op of the next product's B operand.
-template <int KB, int NT>
-__device__ __forceinline__ void bwd_pair(const u32x4 *__restrict__ A, const uint16_t *__restrict__ ht_in,
-                                         uint16_t *__restrict__ dz_out, int64_t stride, const u32x4 (&act)[8][NT],
-                                         int op, int lane, int64_t s_base, u32x4 (&out)[NT]) {
-    const int g = lane >> 4, col = lane & 15;
-    const bool odd = col & 1;
-    f32x4 acc[2][NT];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[h][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-        const u32x4 a0 = A[((2 * op) * KB + kb) * 64 + lane];
-        const u32x4 a1 = A[((2 * op + 1) * KB + kb) * 64 + lane];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            acc[0][nt] = mfma16(a0, act[kb][nt], acc[0][nt]);
-            acc[1][nt] = mfma16(a1, act[kb][nt], acc[1][nt]);
-        }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        // rows mb 16 + 4 g + r of this lane's sample; the pair's loads and
-        // stores cover rows r = 0, 2 (even lane) and 1, 3 (odd lane)
-        const int64_t f0 = (2 * op + h) * 16 + 4 * g + (odd ? 1 : 0);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int64_t s2 = s_base + 16 * nt + (col & ~1);   // first sample of the lane pair
-            // the pair's words of rows (0 | 1) and (2 | 3), both samples; the
-            // same exchange turns them into rows 0 (low) and 1 (high), and 2
-            // and 3, of this lane's own sample
-            const uint32_t r01 = pair_row_word(*reinterpret_cast<const uint32_t *>(ht_in + f0 * stride + s2), odd);
-            const uint32_t r23 =
-                pair_row_word(*reinterpret_cast<const uint32_t *>(ht_in + (f0 + 2) * stride + s2), odd);
-            // the ReLU mask of the layer input (bf16 output > 0; padded samples are 0)
-            const float z0 = (r01 & 0xffffu) != 0u ? acc[h][nt][0] : 0.0f;
-            const float z1 = (r01 >> 16) != 0u ? acc[h][nt][1] : 0.0f;
-            const float z2 = (r23 & 0xffffu) != 0u ? acc[h][nt][2] : 0.0f;
-            const float z3 = (r23 >> 16) != 0u ? acc[h][nt][3] : 0.0f;
-            const uint32_t p01 = pack2(z0, z1), p23 = pack2(z2, z3);
-            out[nt][2 * h + 0] = p01;
-            out[nt][2 * h + 1] = p23;
-            *reinterpret_cast<uint32_t *>(dz_out + f0 * stride + s2) = pair_row_word(p01, odd);
-            *reinterpret_cast<uint32_t *>(dz_out + (f0 + 2) * stride + s2) = pair_row_word(p23, odd);
-        }
-    }
-}
-
-struct BwdArgs {
-    const u32x4 *bwd;
-    const uint16_t *ht;
-    uint16_t *dz;
-    int64_t stride;
-    int64_t n;
-};
-
-// Backward through the layers, split as the training forward: one block of
-// kTrainWaves waves per kTrainNT 16-sample tiles, wave w producing k-blocks
-// kTrainOps w .. kTrainOps (w + 1) - 1 of each layer's input gradient,
-// exchanged through LDS.
-__global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_backward(BwdArgs a) {
-    constexpr int NT = kTrainNT;
-    __shared__ u32x4 xb[2][8][NT][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t s_base = (int64_t)blockIdx.x * (16 * NT);
-    if (s_base >= train_pad(a.n)) return;  // block-uniform
-    const int g = lane >> 4, col = lane & 15;
-    u32x4 act[8][NT];
-    // head gradient as a B operand: outputs 0 and 1 sit in slots 0, 1 of lane group 0
-    const uint16_t *dz5 = a.dz + dz_row(4) * a.stride;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int64_t s = s_base + 16 * nt + col;
-        act[0][nt] = u32x4{0u, 0u, 0u, 0u};
-        if (g == 0) act[0][nt][0] = (uint32_t)dz5[s] | ((uint32_t)dz5[a.stride + s] << 16);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        // j = 0: through W5 (input rows h4, gradient dZ4); j = 3: through W2 (h1, dZ1)
-        const u32x4 *A = a.bwd + bwd_off(j) / 8;
-        const uint16_t *ht_in = a.ht + ht_row(4 - j) * a.stride;
-        uint16_t *dz_out = a.dz + dz_row(3 - j) * a.stride;
-#pragma unroll
-        for (int q = 0; q < kTrainOps; ++q) {
-            const int op = kTrainOps * w + q;
-            u32x4 o[NT];
-            if (j == 0)
-                bwd_pair<1, NT>(A, ht_in, dz_out, a.stride, act, op, lane, s_base, o);
-            else
-                bwd_pair<8, NT>(A, ht_in, dz_out, a.stride, act, op, lane, s_base, o);
-            if (j < 3) {
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) xb[j & 1][op][nt][lane] = o[nt];
-            }
-        }
-        if (j == 3) break;
-        __syncthreads();
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) act[kb][nt] = xb[j & 1][kb][nt][lane];
-    }
-}
-
 // ---- weight gradients ----------------------------------------------------------------
 
-// One block of four waves: a 128 x 128 tile of dW_l[k][o] = sum_s h[k][s]
-// dz[o][s] over one slice of the batch, wave w holding the 64 x 64 quarter
-// (k half w / 2, o half w % 2) as C[k][o] += A[k x 32 samples] B[32 samples x
-// o], plus the bias gradient of its 64 outputs when it holds the layer's
-// first 64 rows. Each 32-sample step stages the tile's 128 h rows and 128 dz
-// rows (64 bytes each) in LDS once for the four waves (double-buffered, one
-// barrier per step); rows are padded to 80 bytes so that a fragment read
-// (16 rows x 16 bytes per lane group) hits 16 distinct bank quadruples.
+// One block of eight waves: a 128 x 128 tile of dW_l[k][o] = sum_s h[k][s]
+// dz[o][s] over one slice of the batch, wave w holding 64 rows k (half w / 4) by 32
+// outputs o (quarter w % 4) as C[k][o] += A[k x 32 samples] B[32 samples x o], plus
+// the bias gradient of its outputs when it holds the layer's first 64 rows. Each
+// stage of 64 samples (two products of 32, in order; samples past the slice as
+// zeros) brings the tile's 128 h rows and 128 dz rows (128 bytes each) to LDS once for
+// all waves (double-buffered, one barrier per stage); rows are padded to 144 bytes
+// so that a fragment read (16 rows x 16 bytes per lane group) hits 16 distinct bank
+// quadruples. 8,192 samples are 256 blocks, one per CU, so what counts is the
+// latency of a stage: 17.0 us, against 20.6 with four waves and 32 samples.
 struct WgradArgs {
     const uint16_t *ht, *dz;
     int64_t stride;
@@ -694,9 +667,10 @@ __device__ __forceinline__ void tile_of(int t, int &l, int &kt, int &ot) {
     l = 4; kt = t; ot = 0;
 }
 constexpr int kTiles = 16;
-constexpr int kWgRow = 40;   // LDS row stride in bf16 elements (80 bytes: 32 samples + padding)
+constexpr int kWgStage = 64;   // samples of a stage
+constexpr int kWgRow = 72;     // LDS row stride in bf16 elements (144 bytes: 64 samples + padding)
 
-__global__ __launch_bounds__(256) void k_mlp_wgrad(WgradArgs a) {
+__global__ __launch_bounds__(512) void k_mlp_wgrad(WgradArgs a) {
     __shared__ __align__(16) uint16_t hs[2][128 * kWgRow];
     __shared__ __align__(16) uint16_t ds[2][128 * kWgRow];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -710,19 +684,20 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(WgradArgs a) {
     const uint16_t *D = a.dz + dz_row(l) * a.stride;
     const int64_t s0 = (int64_t)slice * a.slice_len;
     const int64_t s1 = min(a.n_pad, s0 + a.slice_len);
-    // staging: thread t moves 16-byte part t % 4 of rows t / 4 and 64 + t / 4,
-    // of h and of dz (rows past the layer's inputs or outputs as zeros). A
-    // step's rows are fetched into registers two steps before they are written
-    // to LDS, so each fetch has two steps of products to arrive.
-    const int srow = threadIdx.x >> 2, spart = threadIdx.x & 3;
+    // staging: thread t moves 16-byte part t % 8 of rows t / 8 and 64 + t / 8, of h
+    // and of dz (rows past the layer's inputs or outputs as zeros). A stage's rows
+    // are fetched into registers two stages before they are written to LDS.
+    const int srow = threadIdx.x >> 3, spart = threadIdx.x & 7;
     auto fetch = [&](int64_t s, u32x4 (&r)[4]) {
         if (s >= s1) return;
+        const bool in = s + 8 * spart < s1;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int row = srow + 64 * u;
-            r[2 * u] = k0 + row < Nin ? *reinterpret_cast<const u32x4 *>(H + (int64_t)(k0 + row) * a.stride + s + 8 * spart)
-                                      : u32x4{0u, 0u, 0u, 0u};
-            r[2 * u + 1] = o0 + row < Nout
+            r[2 * u] = in && k0 + row < Nin
+                           ? *reinterpret_cast<const u32x4 *>(H + (int64_t)(k0 + row) * a.stride + s + 8 * spart)
+                           : u32x4{0u, 0u, 0u, 0u};
+            r[2 * u + 1] = in && o0 + row < Nout
                                ? *reinterpret_cast<const u32x4 *>(D + (int64_t)(o0 + row) * a.stride + s + 8 * spart)
                                : u32x4{0u, 0u, 0u, 0u};
         }
@@ -735,55 +710,58 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(WgradArgs a) {
             *reinterpret_cast<u32x4 *>(&ds[buf][row * kWgRow + 8 * spart]) = r[2 * u + 1];
         }
     };
-    const int wk = w >> 1, wo = w & 1;
-    // a wave whose quarter lies past the layer's inputs or outputs only stages
-    const bool live = k0 + 64 * wk < Nin && o0 + 64 * wo < Nout;
+    const int wk = w >> 2, wo = w & 3;
+    // a wave whose part lies past the layer's inputs or outputs only stages
+    const bool live = k0 + 64 * wk < Nin && o0 + 32 * wo < Nout;
     const bool bias = live && k0 + 64 * wk == 0;
     const int g = lane >> 4, col = lane & 15;
-    f32x4 acc[4][4];
+    f32x4 acc[4][2];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum[4] = {0.f, 0.f, 0.f, 0.f};
-    // products of the 32 samples staged in buffer buf
-    auto step = [&](int buf) {
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bsum[2] = {0.f, 0.f};
+    // products of the samples staged in buffer buf
+    auto stage = [&](int buf) {
         if (!live) return;
-        u32x4 av[4], bv[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            av[i] = *reinterpret_cast<const u32x4 *>(&hs[buf][(64 * wk + 16 * i + col) * kWgRow + 8 * g]);
+        for (int x = 0; x < kWgStage; x += 32) {
+            u32x4 av[4], bv[2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            bv[j] = *reinterpret_cast<const u32x4 *>(&ds[buf][(64 * wo + 16 * j + col) * kWgRow + 8 * g]);
-        if (bias) {
+            for (int i = 0; i < 4; ++i)
+                av[i] = *reinterpret_cast<const u32x4 *>(&hs[buf][(64 * wk + 16 * i + col) * kWgRow + x + 8 * g]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 2; ++j)
+                bv[j] = *reinterpret_cast<const u32x4 *>(&ds[buf][(32 * wo + 16 * j + col) * kWgRow + x + 8 * g]);
+            if (bias) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) bsum[j] += bf16_val(bv[j][q] & 0xffffu) + bf16_val(bv[j][q] >> 16);
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) bsum[j] += bf16_val(bv[j][q] & 0xffffu) + bf16_val(bv[j][q] >> 16);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(av[i], bv[j], acc[i][j]);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = mfma16(av[i], bv[j], acc[i][j]);
     };
     u32x4 ra[4], rb[4];
     fetch(s0, ra);
-    fetch(s0 + 32, rb);
+    fetch(s0 + kWgStage, rb);
     put(ra, 0);
-    fetch(s0 + 64, ra);
+    fetch(s0 + 2 * kWgStage, ra);
     __syncthreads();
-    // two steps per pass: buffer 0 holds step s, registers rb step s + 32 and
-    // ra step s + 64
-    for (int64_t s = s0; s < s1; s += 64) {
-        step(0);
-        if (s + 32 < s1) put(rb, 1);
-        fetch(s + 96, rb);
+    // two stages per pass: buffer 0 holds stage s, registers rb the next and ra the
+    // one after
+    for (int64_t s = s0; s < s1; s += 2 * kWgStage) {
+        stage(0);
+        if (s + kWgStage < s1) put(rb, 1);
+        fetch(s + 3 * kWgStage, rb);
         __syncthreads();
-        if (s + 32 >= s1) break;
-        step(1);
-        if (s + 64 < s1) put(ra, 0);
-        fetch(s + 128, ra);
+        if (s + kWgStage >= s1) break;
+        stage(1);
+        if (s + 2 * kWgStage < s1) put(ra, 0);
+        fetch(s + 4 * kWgStage, ra);
         __syncthreads();
     }
     if (!live) return;
@@ -791,8 +769,8 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(WgradArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int o = o0 + 64 * wo + j * 16 + col;
+        for (int j = 0; j < 2; ++j) {
+            const int o = o0 + 32 * wo + j * 16 + col;
             if (o < Nout) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -804,11 +782,11 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(WgradArgs a) {
     if (bias) {
         // lanes col, col+16, col+32, col+48 hold the same output: add the four groups in a fixed order
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < 2; ++j) {
             float v = bsum[j];
             const float v1 = __shfl(v, col + 16), v2 = __shfl(v, col + 32), v3 = __shfl(v, col + 48);
             const float v0 = __shfl(v, col);
-            const int o = o0 + 64 * wo + j * 16 + col;
+            const int o = o0 + 32 * wo + j * 16 + col;
             if (g == 0 && o < Nout) P[off_b(l) + o] = ((v0 + v1) + v2) + v3;
         }
     }
@@ -1157,9 +1135,8 @@ rv_status loss_grad_impl(const void *params, const float *x, const float *d, con
     fa.dz5 = at<uint16_t>(ws, W.dz) + dz_row(4) * W.stride;
     fa.loss_part = at<float>(ws, W.loss_part);
     const int64_t tiles = n_pad / (16 * kTrainNT);   // one block per kTrainNT 16-sample tiles
-    hipLaunchKernelGGL(k_mlp_forward_train, dim3((unsigned)tiles), dim3(kTrainWaves * 64), 0, s, fa);
-    BwdArgs ba{at<u32x4>(params, L.bwd), at<uint16_t>(ws, W.ht), at<uint16_t>(ws, W.dz), W.stride, n};
-    hipLaunchKernelGGL(k_mlp_backward, dim3((unsigned)tiles), dim3(kTrainWaves * 64), 0, s, ba);
+    hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)tiles), dim3(kTrainWaves * 64), 0, s, fa, at<u32x4>(params, L.bwd),
+                       at<uint16_t>(ws, W.dz));
     WgradArgs wa{};
     wa.ht = at<uint16_t>(ws, W.ht);
     wa.dz = at<uint16_t>(ws, W.dz);
@@ -1168,7 +1145,7 @@ rv_status loss_grad_impl(const void *params, const float *x, const float *d, con
     wa.slice_len = slice_len_for(n_pad);
     wa.n_slices = slices_for(n_pad);
     wa.partial = at<float>(ws, W.partial);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kTiles * wa.n_slices)), dim3(256), 0, s, wa);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kTiles * wa.n_slices)), dim3(512), 0, s, wa);
     if (grad)
         hipLaunchKernelGGL(k_reduce_grad, dim3(blocks_for(kNParams, 256)), dim3(256), 0, s, wa.partial, wa.n_slices,
                            grad, at<float>(ws, W.loss_part), tiles, n, loss_out);
