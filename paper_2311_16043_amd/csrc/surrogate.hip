@@ -100,17 +100,49 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
 
 // ---- encoding -----------------------------------------------------------------
 
-// Feature f of the encoding of u[0..5]: u, sin(pi u), cos(pi u), sin(2 pi u),
-// cos(2 pi u), sin(4 pi u), cos(4 pi u) for each scalar; 0 for f >= 42.
-__device__ __forceinline__ float enc_feature(int f, float u0, float u1, float u2, float u3, float u4, float u5) {
-    if (f >= kEnc) return 0.0f;
-    const int a = f / 7, c = f - 7 * a;
-    const float v = a == 0 ? u0 : a == 1 ? u1 : a == 2 ? u2 : a == 3 ? u3 : a == 4 ? u4 : u5;
-    if (c == 0) return v;
-    const int lvl = (c - 1) >> 1;
-    const float w = 3.14159265358979323846f * (float)(1 << lvl);
-    return (c & 1) ? __sinf(w * v) : __cosf(w * v);
+// The encoding of u[0..5] has seven features of each scalar: u, sin(pi u), cos(pi u),
+// sin(2 pi u), cos(2 pi u), sin(4 pi u), cos(4 pi u), features 7 a .. 7 a + 6 of u[a];
+// features kEnc .. 63 are 0. A wave encodes 16 samples (lane col holds sample
+// col = lane % 16's scalars in all four lane groups) as rows of bf16 features in LDS:
+// lane group g evaluates u[g], groups 0 and 1 also u[4 + g]. Each value is computed
+// once, by lanes that take the same path; evaluated where an operand holds it, every
+// lane took both branches of its features and searched each one's scalar (a training
+// step of 8,192 samples: 22.5 us in k_mlp_train, 21.6 so; inference, whose time is
+// the reading of weights from LDS, is as fast either way).
+constexpr int kEncRow = 68;   // bf16 elements of a row (136 bytes: 64 features + padding)
+
+// Zeros in the rows' features past the encoding.
+__device__ __forceinline__ void clear_rows(uint16_t *rows, int lane) {
+    for (int i = lane; i < 16 * kEncRow / 2; i += 64) reinterpret_cast<uint32_t *>(rows)[i] = 0u;
 }
+
+__device__ __forceinline__ void encode_rows(uint16_t *rows, int lane, const float (&u)[6]) {
+    const int g = lane >> 4;
+    uint16_t *const row = rows + (lane & 15) * kEncRow;
+    auto put = [&](int a, float v) {
+        constexpr float pi = 3.14159265358979323846f;
+        const float e[8] = {v, __sinf(pi * v), __cosf(pi * v), __sinf(2.0f * pi * v), __cosf(2.0f * pi * v),
+                            __sinf(4.0f * pi * v), __cosf(4.0f * pi * v), 0.0f};
+#pragma unroll
+        for (int c = 0; c < 7; c += 2) {
+            const uint32_t w = pack2(e[c], e[c + 1]);
+            row[7 * a + c] = (uint16_t)w;
+            if (c < 6) row[7 * a + c + 1] = (uint16_t)(w >> 16);
+        }
+    };
+    put(g, g == 0 ? u[0] : g == 1 ? u[1] : g == 2 ? u[2] : u[3]);
+    if (g < 2) put(4 + g, g == 0 ? u[4] : u[5]);
+}
+
+// k-block kb (0 or 1) of the rows' samples as a B operand (features kfeat).
+__device__ __forceinline__ u32x4 row_kblock(const uint16_t *rows, int kb, int lane) {
+    const uint16_t *const p = rows + (lane & 15) * kEncRow + 32 * kb + 4 * (lane >> 4);
+    const uint2 lo = *reinterpret_cast<const uint2 *>(p), hi = *reinterpret_cast<const uint2 *>(p + 16);
+    return u32x4{lo.x, lo.y, hi.x, hi.y};
+}
+
+// Orders a wave's accesses to its rows.
+__device__ __forceinline__ void rows_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // ---- forward -----------------------------------------------------------------------
 
@@ -222,10 +254,11 @@ __device__ __forceinline__ float to_box(float x, float lo, float hi) {
 }
 
 // The encoded inputs of NT tiles of 16 samples from s_base as B operands
-// (k-blocks 0 and 1 of act; features kfeat).
+// (k-blocks 0 and 1 of act; features kfeat), through the wave's rows.
 template <int kMode, int NT>
-__device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, int lane, u32x4 (&act)[8][NT]) {
-    const int g = lane >> 4, col = lane & 15;
+__device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, int lane, u32x4 (&act)[8][NT],
+                                             uint16_t *rows) {
+    const int col = lane & 15;
     const float lo0 = a.header[0], lo1 = a.header[1], lo2 = a.header[2];
     const float hi0 = a.header[3], hi1 = a.header[4], hi2 = a.header[5];
 #pragma unroll
@@ -270,13 +303,12 @@ __device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, i
                 d0 = a.d[3 * s]; d1 = a.d[3 * s + 1]; d2 = a.d[3 * s + 2];
             }
         }
-        const float u0 = to_box(x0, lo0, hi0), u1 = to_box(x1, lo1, hi1), u2 = to_box(x2, lo2, hi2);
+        const float u[6] = {to_box(x0, lo0, hi0), to_box(x1, lo1, hi1), to_box(x2, lo2, hi2), d0, d1, d2};
+        encode_rows(rows, lane, u);
+        rows_sync();
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-                act[kb][nt][w] = pack2(enc_feature(kfeat(kb, g, 2 * w), u0, u1, u2, d0, d1, d2),
-                                       enc_feature(kfeat(kb, g, 2 * w + 1), u0, u1, u2, d0, d1, d2));
+        for (int kb = 0; kb < 2; ++kb) act[kb][nt] = row_kblock(rows, kb, lane);
+        rows_sync();
     }
 }
 
@@ -290,7 +322,7 @@ __device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, i
 //
 // A block reads all 830 KB of packed weights, and with one block per CU (8,192
 // samples) that and the latency between its layers are the bound: a layer's weights
-// are fetched before the barrier that its inputs wait for. 22.5 us at 8,192 samples,
+// are fetched before the barrier that its inputs wait for. 21.6 us at 8,192 samples,
 // against 18.9 + 20.6 us as two kernels that fetched weights after the barrier, read
 // the masks back from memory and encoded every sample in all eight waves.
 __global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_train(FwdArgs a, const u32x4 *__restrict__ bwd,
@@ -298,6 +330,7 @@ __global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_trai
     constexpr int NT = kTrainNT;
     static_assert(kTrainWaves == 8 && NT == 2, "the encoding is split over the waves");
     __shared__ u32x4 xb[2][8][NT][64];
+    __shared__ __align__(16) uint16_t rows[NT][16 * kEncRow];
     __shared__ float target[16 * NT];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t tile = blockIdx.x;
@@ -310,10 +343,10 @@ __global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_trai
     f32x4 acc[2][NT];
     load_pair<2>(a.fwd + fwd_off(0) / 8, w, lane, f);
 
-    // encode: wave w words 2 (w / 4), 2 (w / 4) + 1 of k-block w % 2 of tile (w / 2) % 2
-    {
-        const int nt = (w >> 1) & 1, kb = w & 1, w0 = 2 * (w >> 2);
-        const int64_t s = s_base + nt * 16 + col;
+    // encode: wave w < 2 tile w
+    if (w < NT) {
+        clear_rows(rows[w], lane);
+        const int64_t s = s_base + w * 16 + col;
         float x0 = 0.f, x1 = 0.f, x2 = 0.f, d0 = 0.f, d1 = 0.f, d2 = 1.f, T = 0.f;
         if (s < a.n) {
             int64_t idx = s;
@@ -324,24 +357,21 @@ __global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_trai
             d0 = a.d[3 * idx]; d1 = a.d[3 * idx + 1]; d2 = a.d[3 * idx + 2];
             T = a.T[idx];
         }
-        const float u0 = to_box(x0, a.header[0], a.header[3]), u1 = to_box(x1, a.header[1], a.header[4]),
-                    u2 = to_box(x2, a.header[2], a.header[5]);
-        uint32_t *const out = reinterpret_cast<uint32_t *>(&xb[1][kb][nt][lane]) + w0;
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            out[q] = pack2(enc_feature(kfeat(kb, g, 2 * (w0 + q)), u0, u1, u2, d0, d1, d2),
-                           enc_feature(kfeat(kb, g, 2 * (w0 + q) + 1), u0, u1, u2, d0, d1, d2));
-        if (kb == 0 && w0 == 0 && g == 0) target[nt * 16 + col] = T;
+        const float u[6] = {to_box(x0, a.header[0], a.header[3]), to_box(x1, a.header[1], a.header[4]),
+                            to_box(x2, a.header[2], a.header[5]), d0, d1, d2};
+        rows_sync();
+        encode_rows(rows[w], lane, u);
+        if (g == 0) target[w * 16 + col] = T;
     }
     __syncthreads();
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) act[kb][nt] = xb[1][kb][nt][lane];
+        for (int nt = 0; nt < NT; ++nt) act[kb][nt] = row_kblock(rows[nt], kb, lane);
     if (w < 2) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            store_kblock(a.ht + ht_row(0) * a.stride, a.stride, xb[1][w][nt][lane], w, lane, s_base + 16 * nt,
+            store_kblock(a.ht + ht_row(0) * a.stride, a.stride, row_kblock(rows[nt], w, lane), w, lane, s_base + 16 * nt,
                          a.n);
     }
 
@@ -578,6 +608,7 @@ template <int kMode>
 __global__ __launch_bounds__(kInferWaves * 64, 1) void k_mlp_forward(FwdArgs a) {
     constexpr int NT = kInferNT;
     __shared__ u32x4 wbuf[2][kChunkVec];
+    __shared__ __align__(16) uint16_t rows[kInferWaves][16 * kEncRow];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int g = lane >> 4, col = lane & 15;
     // every wave takes part in the loads and barriers; waves past the end
@@ -587,7 +618,9 @@ __global__ __launch_bounds__(kInferWaves * 64, 1) void k_mlp_forward(FwdArgs a) 
     const float *master = a.master;
     load_chunk(F + fwd_off(0) / 8, 2048, wbuf[0], wv, lane);
     u32x4 act[8][NT];
-    encode_tiles<kMode, NT>(a, s_base, lane, act);
+    clear_rows(rows[wv], lane);
+    rows_sync();
+    encode_tiles<kMode, NT>(a, s_base, lane, act, rows[wv]);
     chunk_barrier();
     // layer 1 (64 -> 256) from buffer 0; layer 2's first half loads into buffer 1
     load_chunk(F + fwd_off(1) / 8, kChunkVec, wbuf[1], wv, lane);
