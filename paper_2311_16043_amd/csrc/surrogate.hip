@@ -536,55 +536,60 @@ __device__ __forceinline__ void chunk_barrier() {
     __syncthreads();
 }
 
-// Output pair OP0 + o of a layer (the same arithmetic as hidden_layer) from
-// the LDS chunk holding the A operands of pairs OP0, OP0 + 1, ...
-
-template <int KB, int NT, int OP0>
-__device__ __forceinline__ void layer_ops_lds_one(const u32x4 *A, int o, const float *__restrict__ bias,
-                                                  const u32x4 (&act)[8][NT], u32x4 (&out)[8][NT], int lane) {
+// Output pairs [OP0, OP0 + NOP) of a layer (the same arithmetic as multiply_pair's)
+// from the LDS chunk holding their A operands. Each k-block's two operands are read
+// two k-blocks before its products: 2.93 ms for 6.4M queries with the reads right
+// before the products, 2.63 one k-block ahead, 2.56 two (the scheduling groups hold
+// the reads there; with half of them left out 2.01, with the epilogue left out 2.48).
+template <int KB, int NT, int OP0, int NOP>
+__device__ __forceinline__ void layer_ops_lds(const u32x4 *A, const float *__restrict__ bias,
+                                              const u32x4 (&act)[8][NT], u32x4 (&out)[8][NT], int lane) {
     const int g = lane >> 4;
-    f32x4 acc[2][NT];
+    // the operands of the next two k-blocks are read while this one is multiplied
+    u32x4 n0 = A[lane], n1 = A[KB * 64 + lane], m0 = A[64 + lane], m1 = A[(KB + 1) * 64 + lane];
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int o = 0; o < NOP; ++o) {
+        f32x4 acc[2][NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[h][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-        const u32x4 a0 = A[((2 * o) * KB + kb) * 64 + lane];
-        const u32x4 a1 = A[((2 * o + 1) * KB + kb) * 64 + lane];
+            for (int nt = 0; nt < NT; ++nt) acc[h][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            acc[0][nt] = mfma16(a0, act[kb][nt], acc[0][nt]);
-            acc[1][nt] = mfma16(a1, act[kb][nt], acc[1][nt]);
+        for (int kb = 0; kb < KB; ++kb) {
+            const u32x4 a0 = n0, a1 = n1;
+            n0 = m0;
+            n1 = m1;
+            const int on = kb + 2 < KB ? o : o + 1, kn = kb + 2 < KB ? kb + 2 : kb + 2 - KB;
+            if (on < NOP) {
+                m0 = A[((2 * on) * KB + kn) * 64 + lane];
+                m1 = A[((2 * on + 1) * KB + kn) * 64 + lane];
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                acc[0][nt] = mfma16(a0, act[kb][nt], acc[0][nt]);
+                acc[1][nt] = mfma16(a1, act[kb][nt], acc[1][nt]);
+            }
+            if (on < NOP) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2 * NT, 0);
         }
-        // per k-block: its two LDS reads, then its products
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NT, 0);
-    }
-    // bias in FP32, then the bf16 pair, then the ReLU on the packed words
+        // bias in FP32, then the bf16 pair, then the ReLU on the packed words
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const float4 bv = *reinterpret_cast<const float4 *>(bias + (2 * (OP0 + o) + h) * 16 + 4 * g);
+        for (int h = 0; h < 2; ++h) {
+            const float4 bv = *reinterpret_cast<const float4 *>(bias + (2 * (OP0 + o) + h) * 16 + 4 * g);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            out[OP0 + o][nt][2 * h + 0] = relu_bf16x2(pack2(acc[h][nt][0] + bv.x, acc[h][nt][1] + bv.y));
-            out[OP0 + o][nt][2 * h + 1] = relu_bf16x2(pack2(acc[h][nt][2] + bv.z, acc[h][nt][3] + bv.w));
+            for (int nt = 0; nt < NT; ++nt) {
+                out[OP0 + o][nt][2 * h + 0] = relu_bf16x2(pack2(acc[h][nt][0] + bv.x, acc[h][nt][1] + bv.y));
+                out[OP0 + o][nt][2 * h + 1] = relu_bf16x2(pack2(acc[h][nt][2] + bv.z, acc[h][nt][3] + bv.w));
+            }
         }
     }
 }
 
 // A 256 -> 256 layer from two LDS chunks (output pairs 0-3, then 4-7);
 // `between` runs once the first half is done (the chunk hand-over). The
-// output array is local, as in hidden_layer, so the input array's registers
-// are reused as soon as the layer ends.
-// Output pairs [OP0, OP0 + NOP) of a layer from one LDS chunk.
-template <int KB, int NT, int OP0, int NOP>
-__device__ __forceinline__ void layer_ops_lds(const u32x4 *A, const float *__restrict__ bias,
-                                              const u32x4 (&act)[8][NT], u32x4 (&out)[8][NT], int lane) {
-#pragma unroll
-    for (int o = 0; o < NOP; ++o) layer_ops_lds_one<KB, NT, OP0>(A, o, bias, act, out, lane);
-}
-
+// output array is local, so the input array's registers are reused as soon as
+// the layer ends.
 template <int NT, class Between>
 __device__ __forceinline__ void hidden_layer_lds(const u32x4 *A_lo, const u32x4 *A_hi, const float *__restrict__ bias,
                                                  u32x4 (&act)[8][NT], int lane, Between between) {
@@ -601,7 +606,7 @@ __device__ __forceinline__ void hidden_layer_lds(const u32x4 *A_lo, const u32x4 
 // Chunks, in 16-byte vectors of the packed forward operands: layer 1 whole
 // (2,048), layers 2-4 in halves of four output pairs (4,096 each), the head
 // (512). Chunk c is multiplied from buffer c % 2 while chunk c + 1 loads into
-// the other. A k-block's two LDS reads are scheduled right before its
+// the other. A k-block's two LDS reads are scheduled two k-blocks before its
 // products: hoisted further, as the compiler otherwise does, they spill the
 // activations.
 template <int kMode>
