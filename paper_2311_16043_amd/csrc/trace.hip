@@ -78,12 +78,17 @@ constexpr int kLeafMin = 32;
 // Resident blocks per CU of the persistent traversal. Its waves share the CU's
 // vector-memory path, which they keep full, and the caches: more of them only thin
 // those out, and with few pools they also end further apart. 5 / 4 / 3 blocks:
-// 40.0 / 42.0 / 50.3 ms at 300,000 Gaussians x 256, 59.2 / 58.4 / 69.0 ms at
-// 1.2M x 64, 77.1 / 67.5 / 79.6 ms at 3M x 16; 4.48 / 4.76 / 5.44 ms at
+// 40.0 / 42.0 / 50.3 ms at 300,000 Gaussians x 256; 4.48 / 4.76 / 5.44 ms at
 // 100,000 x 128, 1.16 / 1.17 / 1.23 ms at 50,000 x 64, 774 / 744 / 743 us at
-// 30,000 x 64 (six: 43.8 ms at 300,000 x 256).
+// 30,000 x 64 (six: 43.8 ms at 300,000 x 256). On large trees the fewer directions
+// a Gaussian has, the more Gaussians the pools in flight cover, and the tree they
+// touch outgrows the L2: 5 / 4 blocks on one surface of 3M Gaussians 110 / 94 ms x 16
+// and 407 / 353 x 64, of 1.2M 173 / 157 x 128; in 20 objects of 150,000 46.3 / 44.8
+// x 16, 168.4 / 169.9 x 64, 644 / 667 x 256 and 2,525 / 2,651 x 1,024 (six: 2,820).
+// The line lies where the one gains about ten times what the other loses.
 constexpr int kStreamBlocksPerCu = 5, kStreamBlocksDeep = 4, kStreamBlocksFew = 3;
 constexpr int64_t kFewPools = 40000, kDeepStreamGaussians = int64_t(1) << 20;
+constexpr int kDeepStreamDirs = 96;
 // Up to this many pools every wave takes one pool and the hardware hands out the
 // blocks. The queues' counters, on few lines, serve about one wave in 50 ns: with
 // queues / so, 463 / 202 us at 5,003 x 33 (2,607 pools), 629 / 112 us at 5,000 x 64,
@@ -970,7 +975,7 @@ rv_status validate_trace(const char *fn, const void *bvh, const rv_gaussians *g,
 // Blocks of a persistent traversal grid: what the device holds at once, up
 // to the blocks per CU above (a multiple of 8, at least 8: every XCD queue
 // has blocks), no more than the pools need.
-int64_t stream_blocks(int64_t n_pools, int64_t n) {
+int64_t stream_blocks(int64_t n_pools, int64_t n, int K) {
     static std::atomic<int> cached[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = -1;
@@ -990,7 +995,7 @@ int64_t stream_blocks(int64_t n_pools, int64_t n) {
     }
     const int cus = nb / 256;
     const int per_cu = std::min(nb % 256, n_pools <= kFewPools           ? kStreamBlocksFew
-                                          : n >= kDeepStreamGaussians ? kStreamBlocksDeep
+                                          : n >= kDeepStreamGaussians && K <= kDeepStreamDirs ? kStreamBlocksDeep
                                                                       : kStreamBlocksPerCu);
     int64_t want = std::min<int64_t>((int64_t)cus * per_cu, (n_pools + kWavesPerBlock - 1) / kWavesPerBlock);
     want = (want + kXcds - 1) / kXcds * kXcds;
@@ -1015,7 +1020,7 @@ void launch_trace_list(const void *bvh, const rv_gaussians *g, const float *dirs
     cc.refill = refill_lanes(g->n);
     if (queues) {
         launch_clear_queues(queues, stream);
-        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n)), dim3(kTraceBlock), 0, stream,
+        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n, K)), dim3(kTraceBlock), 0, stream,
                            at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), g->mean,
                            c.dir_mode ? g->normal : nullptr, g->log_scale, g->n, dirs, K, cc, ids, n_list, count,
                            id_offset, out_by_value ? 1 : 0, (int64_t)0, queues, out);
@@ -1057,7 +1062,7 @@ void launch_trace_stream(const void *bvh, const rv_gaussians *g, const float *di
     const bool one = n_pools <= kOnePoolWaves;
     if (!one) launch_clear_queues(queues, s);
     const unsigned blocks =
-        (unsigned)(one ? (n_pools + kWavesPerBlock - 1) / kWavesPerBlock : stream_blocks(n_pools, g->n));
+        (unsigned)(one ? (n_pools + kWavesPerBlock - 1) / kWavesPerBlock : stream_blocks(n_pools, g->n, K));
     hipLaunchKernelGGL((one ? k_trace_stream<kCount, true> : k_trace_stream<kCount, false>), dim3(blocks),
                        dim3(kTraceBlock), 0, s, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4),
                        at<float4>(bvh, L.leaf_rec), at<float4>(bvh, L.origins), dirs, g->n, K, cc, m_lo, m_hi,
@@ -1231,7 +1236,7 @@ extern "C" rv_status rv_trace_visibility_backward(const void *bvh, const rv_gaus
     }
     if (mem && n_pools > kAdjOnePoolWaves) {
         const auto kernel = n_pools > kFewPools ? k_adjoint_trace<false, true> : k_adjoint_trace<false, false>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)stream_blocks(n_pools, n)), dim3(kTraceBlock), 0, s,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)stream_blocks(n_pools, n, K)), dim3(kTraceBlock), 0, s,
                            at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), pools,
                            int64_t(0), n_pools, c, queues, grad_vis_ray, grad_vis_mean, vis_ray_fwd, grad_opacity,
                            grad_mean, grad_log_scale, sc);
