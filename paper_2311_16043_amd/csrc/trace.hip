@@ -26,19 +26,6 @@ namespace rv {
 namespace {
 
 constexpr int kWavesPerBlock = kTraceBlock / 64;
-// Logical block of dispatched block b in rounds of kXcds chunks of C
-// consecutive logical blocks: XCD x (b % 8 == x) takes chunk x of each round,
-// so the XCDs walk the logical order side by side (each on a compact part of
-// the scene at a time) and finish together; blocks past the last full round
-// keep the contiguous split. A bijection on [0, nb).
-template <int C>
-__device__ __forceinline__ int64_t xcd_chunk_block(int64_t b, int64_t nb) {
-    constexpr int64_t kRound = int64_t(kXcds) * C;
-    const int64_t full = nb / kRound * kRound;
-    if (b >= full) return full + xcd_block(b - full, nb - full);
-    const int64_t x = b % kXcds, r = b / kXcds;
-    return ((r / C) * kXcds + x) * C + r % C;
-}
 
 // ---- pooled traversal -----------------------------------------------------------
 //
@@ -1020,7 +1007,8 @@ void launch_trace_list(const void *bvh, const rv_gaussians *g, const float *dirs
     cc.refill = refill_lanes(g->n);
     if (queues) {
         launch_clear_queues(queues, stream);
-        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n, K)), dim3(kTraceBlock), 0, stream,
+        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n, K)), dim3(kTraceBlock), 0,
+                           stream,
                            at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), g->mean,
                            c.dir_mode ? g->normal : nullptr, g->log_scale, g->n, dirs, K, cc, ids, n_list, count,
                            id_offset, out_by_value ? 1 : 0, (int64_t)0, queues, out);
