@@ -230,9 +230,9 @@ __device__ __forceinline__ float leaf_factor(const float4 *__restrict__ rec, int
                                              int32_t self, int32_t self_leaf_m1, const Cuts &c, OnHit &on_hit,
                                              float T_before) {
     if (m1 == self_leaf_m1) return 1.0f;   // the source's own leaf, known by sorted position
-    const float4 r0 = rec[kLeafF4 * m1 + kLeafF4 + 0];
-    const float4 r1 = rec[kLeafF4 * m1 + kLeafF4 + 1];
-    const float4 r2 = rec[kLeafF4 * m1 + kLeafF4 + 2];
+    // (in 64 bits: the record's first word passes 2^31 from leaf 715,827,883 on)
+    const float4 *r = rec + ((int64_t)kLeafF4 * m1 + kLeafF4);
+    const float4 r0 = r[0], r1 = r[1], r2 = r[2];
     const int32_t src = __float_as_int(r2.w);
     const f3 w0 = mk(r1.x, r1.y, r1.z), w1 = mk(r2.x, r2.y, r2.z);
     const f3 w2 = r1.w * cross(w0, w1);
