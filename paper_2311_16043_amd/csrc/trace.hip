@@ -677,12 +677,14 @@ struct GradRecord {
 template <bool kChain>
 struct AdjStage {
     static constexpr int kSize = kChain ? kAdjStageChain : kAdjStage;
-    struct Lds {
+    // (a block has an array of them, and records are stored as float4)
+    struct alignas(16) Lds {
         float val[kSize * 4];
         int32_t leaf[kSize];
         int32_t next[kChain ? kSize : 1];   // the next record of a chain, -1 at its end
         int32_t last[kChain ? kSize : 1];   // the last record of a hash class; then the chains' heads
     };
+    static_assert(sizeof(Lds) % 16 == 0, "every wave's records must be aligned as float4");
     Lds *s;
     int n;   // wave-uniform
     // Orders the wave's accesses to its stage.
@@ -768,7 +770,7 @@ __global__ __launch_bounds__(kTraceBlock, kOnePool ? 4 : kStreamBlocksPerCu) voi
     AdjScratch sc) {
     __shared__ Pair stk[kStreamRing * kTraceBlock];
     __shared__ Pair fifo[kFifo * kTraceBlock];
-    __shared__ __align__(16) typename AdjStage<kChain>::Lds stage_lds[kWavesPerBlock];
+    __shared__ typename AdjStage<kChain>::Lds stage_lds[kWavesPerBlock];
     const int64_t n = pools.m_hi;
     if (!tree_matches(header, n)) {
         // a tree built for another Gaussian set: every gradient is NaN
