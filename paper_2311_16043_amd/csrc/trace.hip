@@ -6,9 +6,9 @@
 // Work mapping. Rays come in pools (see the pooled traversal below): 64
 // Gaussians adjacent in Morton (sorted-leaf) order times one direction for the
 // all-ray kernels (the forward, which also serves the SH projection, and the
-// adjoint), and 64 or 256 consecutive entries for the list kernel. Up to
-// kOnePoolWaves pools (kAdjOnePoolWaves in the adjoint) every wave takes one;
-// beyond, a persistent grid takes them from eight queues, one per XCD, each a
+// adjoint), and 64 or 256 consecutive entries for the list kernel. In small
+// launches every wave takes one pool; in larger ones a persistent grid takes them from
+// eight queues, one per XCD (see Route). In the largest each queue is a
 // contiguous eighth of the Morton order, so each L2 sees a compact part of the
 // tree; a wave whose queue is spent takes pools from the others, so no XCD
 // idles while another still holds work. A wave keeps its lanes supplied
@@ -67,7 +67,7 @@ constexpr int kLeafMin = 32;
 // those out, and with few pools they also end further apart. 5 / 4 / 3 blocks:
 // 40.0 / 42.0 / 50.3 ms at 300,000 Gaussians x 256; 4.48 / 4.76 / 5.44 ms at
 // 100,000 x 128, 1.16 / 1.17 / 1.23 ms at 50,000 x 64, 774 / 744 / 743 us at
-// 30,000 x 64 (six: 43.8 ms at 300,000 x 256). On large trees the fewer directions
+// 30,000 x 64 (six: 43.8 ms at 300,000 x 256; all by XcdQueue). On large trees the fewer directions
 // a Gaussian has, the more Gaussians the pools in flight cover, and the tree they
 // touch outgrows the L2: 5 / 4 blocks on one surface of 3M Gaussians 110 / 94 ms x 16
 // and 407 / 353 x 64, of 1.2M 173 / 157 x 128; in 20 objects of 150,000 46.3 / 44.8
@@ -76,12 +76,29 @@ constexpr int kLeafMin = 32;
 constexpr int kStreamBlocksPerCu = 5, kStreamBlocksDeep = 4, kStreamBlocksFew = 3;
 constexpr int64_t kFewPools = 40000, kDeepStreamGaussians = int64_t(1) << 20;
 constexpr int kDeepStreamDirs = 96;
-// Up to this many pools every wave takes one pool and the hardware hands out the
-// blocks. The queues' counters, on few lines, serve about one wave in 50 ns: with
-// queues / so, 463 / 202 us at 5,003 x 33 (2,607 pools), 629 / 112 us at 5,000 x 64,
-// 540 / 470 us at 20,000 x 64, 726 / 790 us at 30,000 x 64 (the lanes of a wave
-// that has one pool idle towards its end).
-constexpr int64_t kOnePoolWaves = 24000;
+// How a launch's waves come to their pools. The counters of XcdQueue, on few lines,
+// serve about one wave in 50 ns, and every wave adds to all eight to find them spent.
+//   kOnePool  every wave takes one pool and the hardware hands out the blocks; the
+//             lanes of a wave idle towards its end, and so do waves until their
+//             block's last has ended.
+//   kDealt    a persistent grid takes the pools from DealQueue.
+//   kQueues   a persistent grid takes the pools from XcdQueue.
+// kOnePool / kDealt in us: surfaces 79 / 85 at 1,000 Gaussians x 600 (9,600 pools),
+// 207 / 173 at 10,000 x 64, 248 / 246 at 10,000 x 100, 468 / 386 at 20,000 x 64; a cloud
+// in which a ray crosses hundreds of Gaussians (10 % opaque, standard deviations 0.07 to
+// 0.37 of a side of 2) 12.5 / 11.7 ms at 10,000 x 64, 36.1 / 30.5 at 20,000 x 64. On up
+// to 256 Gaussians rays are so short that even a counter each is in the way (150 / 212
+// at 64 x 20,000), and a tree that outgrows the caches wants its pools in order
+// (1,889 / 2,146 at 1.2M x 1). kDealt / kQueues: surfaces 390 / 422 at 24,000 x 64 and
+// 599 / 715 at 30,000 x 64, but clouds 1,414 / 1,334 at 12,000 x 128 and, as above with
+// deviations divided by e, 20.1 / 17.4 ms at 30,000 x 64.
+enum class Route { kOnePool, kDealt, kQueues };
+constexpr int64_t kOnePoolWaves = 10000, kDealtPools = 24000, kFewGaussians = 256;
+inline Route all_ray_route(int64_t n_pools, int64_t n) {
+    if (n_pools > kDealtPools) return Route::kQueues;
+    const bool dealt = n_pools > kOnePoolWaves && n > kFewGaussians && n < kDeepStreamGaussians;
+    return dealt ? Route::kDealt : Route::kOnePool;
+}
 
 // Visits that a walk makes at most between two looks at its budget (a malformed
 // tree with a cycle ends then, with NaN).
@@ -114,16 +131,21 @@ struct RaySetup {
 // first, so that adjacent Gaussians share that XCD's L2; once the range is
 // spent it takes from the other ranges in turn, so no XCD idles while another
 // still holds work.
+// DealQueue: the pools are dealt to the XCDs in chunks of kDeal consecutive ones, with
+// a counter each; a wave's first pool follows from its place in the grid, and it
+// leaves once its XCD's pools are spent. Chunks this small share a launch out as
+// evenly as taking from other ranges does, and a wave adds to one counter at its
+// end instead of to eight.
 // RangeQueue: a fixed run of consecutive pools.
 constexpr int kQueueStride = 4;   // the eight counters fill 256 bytes
 struct XcdQueue {
     unsigned long long *ctrs;  // kXcds counters
     int64_t n_pools;
     int home, turn;  // the range being drained is (home + turn) % kXcds
-    __device__ __forceinline__ void init(unsigned long long *c, int64_t np, int x) {
+    __device__ __forceinline__ void init(unsigned long long *c, int64_t np, uint32_t block, uint32_t) {
         ctrs = c;
         n_pools = np;
-        home = x;
+        home = (int)(block % kXcds);
         turn = 0;
     }
     // Next pool in p, false once every range is spent. Called in wave-uniform
@@ -144,6 +166,35 @@ struct XcdQueue {
     }
 };
 
+// Chunks of 4 / 16 / 64 pools: 484 / 471 / 402 us at 20,000 Gaussians x 64 (20,032
+// pools), 1,126 / 1,087 / 854 at 40,000 x 64.
+constexpr uint32_t kDeal = 64;
+struct DealQueue {
+    unsigned long long *ctr;
+    int64_t n_pools;
+    uint32_t xcd, own, held;   // of its XCD's pools: the wave's first; how many are a wave's first
+    __device__ __forceinline__ void init(unsigned long long *c, int64_t np, uint32_t block, uint32_t blocks) {
+        xcd = block % kXcds;
+        ctr = c + kQueueStride * xcd;
+        n_pools = np;
+        own = block / kXcds * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        held = blocks / kXcds * kWavesPerBlock;
+    }
+    __device__ __forceinline__ bool take(int64_t &p) {
+        uint32_t t = own;
+        if (t < held) {
+            own = held;
+        } else {
+            const int lane = threadIdx.x & 63;
+            if (lane == __builtin_amdgcn_readfirstlane(lane)) t = held + (uint32_t)atomicAdd(ctr, 1ull);
+            t = __builtin_amdgcn_readfirstlane(t);
+        }
+        const uint32_t round = t / kDeal;
+        p = (int64_t)((round * kXcds + (xcd + round) % kXcds) * kDeal + t % kDeal);
+        return p < n_pools;
+    }
+};
+
 struct RangeQueue {
     int64_t next, end;
     __device__ __forceinline__ bool take(int64_t &p) {
@@ -152,12 +203,39 @@ struct RangeQueue {
     }
 };
 
+// When a wave's lanes without a ray take new ones: always once no lane has a ray;
+// else on a filled chip once c.refill lanes are idle, so that the ray setup runs for
+// several lanes at a time.
+template <class Queue>
+struct Refill {
+    __device__ __forceinline__ bool now(uint64_t idle, int lanes) { return __popcll(idle) >= lanes || ~idle == 0; }
+};
+// From a DealQueue once the idle lanes have cost as much as about forty iterations of
+// the whole wave: the rays of one pool run side by side, and mixed with another's they
+// share fewer lines, which costs small launches more than idle lanes do unless the
+// pool's last rays are long. With 12 idle lanes / 1,024 / 2,048 / 4,096 / 8,192
+// lane-iterations / never, in us: surfaces 165 / 162 / 135 / 134 / 134 / 133 at 5,000
+// Gaussians x 128 and 502 / 576 / 599 / 571 / 511 / 502 at 30,000 x 64, a cloud
+// (deviations as under Route, divided by e) 6.1 / 6.3 / 6.2 / 6.1 / 6.6 / 7.5 ms at
+// 12,000 x 100 and, of 0.01 to 0.05, 1.06 / 1.12 / 1.18 / 1.33 / 1.59 / 1.39 ms.
+template <>
+struct Refill<DealQueue> {
+    static constexpr int kIdleMax = 2048;
+    int idled = 0;
+    __device__ __forceinline__ bool now(uint64_t idle, int) {
+        idled += __popcll(idle);
+        if (idled < kIdleMax && ~idle != 0) return false;
+        idled = 0;
+        return true;
+    }
+};
+
 // Trace the rays of the pools the queue hands out with the lanes of one
 // wave. With kAhead the words of a lane's next node are fetched as soon as the
 // node is known, while leaves are tested: for launches that leave the chip's
 // memory path idle (5,000 Gaussians x 33: 202 against 210 us; a filled chip runs up
-// to 5 % slower so). Once c.refill lanes are without a ray (or no lane has one), those
-// lanes take the next rays of the current pool; when the pool is spent the
+// to 5 % slower so). Lanes without a ray
+// take the next rays of the current pool (see Refill); when the pool is spent the
 // wave takes the next pool at once, so lanes stay supplied across pool
 // boundaries. A finished
 // ray writes its T to out[r.out] (when out is given). stk and my_fifo are
@@ -188,13 +266,12 @@ __device__ __forceinline__ void stream_rays(const float4 *__restrict__ nodes4, c
     // wave-uniform pool state
     int next = 0, pool_n = 0;
     bool more = true;
+    Refill<Queue> refill;
 
     for (uint32_t round = 1;; ++round) {
-        // refill idle lanes, moving on to further pools while lanes are idle;
-        // only once c.refill lanes are idle (or none holds a ray), so that
-        // the ray setup runs for several lanes at a time
+        // refill idle lanes, moving on to further pools while lanes are idle
         uint64_t need = __ballot(wk.idle());
-        if (__popcll(need) < c.refill && ~need != 0) need = 0;
+        if (!refill.now(need, c.refill)) need = 0;
         while (need != 0 && more) {
             if (next >= pool_n) {
                 int64_t p;
@@ -384,10 +461,10 @@ struct ListPools : ListSource {
 // for [0, n)): with kOnePool one pool per wave (consecutive blocks of pools on one
 // XCD), else through per-XCD queues of pools. The grid of the latter is persistent (a
 // multiple of 8 blocks, about what the device holds at once) and block b
-// serves the queue of XCD b % 8 (round-robin dispatch), whose range is a
+// serves the queue of XCD b % 8 (round-robin dispatch). With kQueues its range is a
 // contiguous eighth of the pools: each L2 sees a compact part of the tree
 // until its range is spent and its waves help with the other ranges.
-template <bool kCount, bool kOnePool>
+template <bool kCount, Route kRoute>
 __global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_stream(const float *__restrict__ header,
                                                               const float4 *__restrict__ nodes4,
                                                               const float4 *__restrict__ rec,
@@ -426,17 +503,17 @@ __global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_strea
     pools.inv_nv = 1.0f;
     const int64_t n_pools = ((m_hi - m_lo + 63) / 64) * (int64_t)pools.n_chunks;
     int64_t cn = 0, cl = 0, ch = 0;
-    if constexpr (kOnePool) {
+    if constexpr (kRoute == Route::kOnePool) {
         RangeQueue q;
         q.next = xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + (threadIdx.x >> 6);
         q.end = min(n_pools, q.next + 1);
         stream_rays<kCount, true>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, vis_ray, cn, cl,
                                   ch);
     } else {
-        XcdQueue q;
-        q.init(queues, n_pools, (int)(blockIdx.x % kXcds));
-        stream_rays<kCount, false>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, vis_ray, cn, cl,
-                                   ch);
+        std::conditional_t<kRoute == Route::kDealt, DealQueue, XcdQueue> q;
+        q.init(queues, n_pools, blockIdx.x, gridDim.x);
+        stream_rays<kCount, kRoute == Route::kDealt>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x,
+                                                     vis_ray, cn, cl, ch);
     }
     if (kCount) {
         atomicAdd(totals + 0, (unsigned long long)cn);
@@ -468,7 +545,7 @@ __global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_list(
     using Queue = typename std::conditional<kQueue, XcdQueue, RangeQueue>::type;
     Queue q;
     if constexpr (kQueue) {
-        q.init(queues, n_pools, (int)(blockIdx.x % kXcds));
+        q.init(queues, n_pools, blockIdx.x, gridDim.x);
     } else {
         const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
         q.next = w * run;
@@ -792,7 +869,7 @@ __global__ __launch_bounds__(kTraceBlock, kOnePool ? 4 : kStreamBlocksPerCu) voi
         queue.next = first + xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + wv;
         queue.end = min(n_pools, queue.next + 1);
     } else {
-        queue.init(queues, n_pools, (int)(blockIdx.x % kXcds));
+        queue.init(queues, n_pools, blockIdx.x, gridDim.x);
     }
 
     Walk<kStreamRing> wk;
@@ -962,9 +1039,9 @@ rv_status validate_trace(const char *fn, const void *bvh, const rv_gaussians *g,
 
 
 // Blocks of a persistent traversal grid: what the device holds at once, up
-// to the blocks per CU above (a multiple of 8, at least 8: every XCD queue
-// has blocks), no more than the pools need.
-int64_t stream_blocks(int64_t n_pools, int64_t n, int K) {
+// to the blocks per CU above, kStreamBlocksFew with `few` (a multiple of 8, at
+// least 8: every XCD queue has blocks), no more than the pools need.
+int64_t stream_blocks(int64_t n_pools, int64_t n, int K, bool few) {
     static std::atomic<int> cached[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = -1;
@@ -974,7 +1051,7 @@ int64_t stream_blocks(int64_t n_pools, int64_t n, int K) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) != hipSuccess ||
             cus <= 0)
             cus = 256;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_trace_stream<false, false>, kTraceBlock, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_trace_stream<false, Route::kQueues>, kTraceBlock, 0) !=
                 hipSuccess ||
             per_cu <= 0)
             per_cu = 4;
@@ -983,9 +1060,9 @@ int64_t stream_blocks(int64_t n_pools, int64_t n, int K) {
         if (dev >= 0 && dev < 64) cached[dev].store(nb);
     }
     const int cus = nb / 256;
-    const int per_cu = std::min(nb % 256, n_pools <= kFewPools           ? kStreamBlocksFew
+    const int per_cu = std::min(nb % 256, few ? kStreamBlocksFew
                                           : n >= kDeepStreamGaussians && K <= kDeepStreamDirs ? kStreamBlocksDeep
-                                                                      : kStreamBlocksPerCu);
+                                                                                              : kStreamBlocksPerCu);
     int64_t want = std::min<int64_t>((int64_t)cus * per_cu, (n_pools + kWavesPerBlock - 1) / kWavesPerBlock);
     want = (want + kXcds - 1) / kXcds * kXcds;
     return std::max<int64_t>(want, kXcds);
@@ -1009,9 +1086,8 @@ void launch_trace_list(const void *bvh, const rv_gaussians *g, const float *dirs
     cc.refill = refill_lanes(g->n);
     if (queues) {
         launch_clear_queues(queues, stream);
-        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n, K)), dim3(kTraceBlock), 0,
-                           stream,
-                           at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), g->mean,
+        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n, K, pools <= kFewPools)),
+                           dim3(kTraceBlock), 0, stream, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), g->mean,
                            c.dir_mode ? g->normal : nullptr, g->log_scale, g->n, dirs, K, cc, ids, n_list, count,
                            id_offset, out_by_value ? 1 : 0, (int64_t)0, queues, out);
         return;
@@ -1049,14 +1125,17 @@ void launch_trace_stream(const void *bvh, const rv_gaussians *g, const float *di
     auto *queues = static_cast<unsigned long long *>(ws);
     Cuts cc = c;
     cc.refill = refill_lanes(g->n);
-    const bool one = n_pools <= kOnePoolWaves;
-    if (!one) launch_clear_queues(queues, s);
-    const unsigned blocks =
-        (unsigned)(one ? (n_pools + kWavesPerBlock - 1) / kWavesPerBlock : stream_blocks(n_pools, g->n, K));
-    hipLaunchKernelGGL((one ? k_trace_stream<kCount, true> : k_trace_stream<kCount, false>), dim3(blocks),
-                       dim3(kTraceBlock), 0, s, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4),
-                       at<float4>(bvh, L.leaf_rec), at<float4>(bvh, L.origins), dirs, g->n, K, cc, m_lo, m_hi,
-                       by_leaf ? 1 : 0, queues, vis_ray, totals);
+    const Route route = all_ray_route(n_pools, g->n);
+    int64_t blocks = (n_pools + kWavesPerBlock - 1) / kWavesPerBlock;
+    auto kernel = k_trace_stream<kCount, Route::kOnePool>;
+    if (route != Route::kOnePool) {
+        launch_clear_queues(queues, s);
+        blocks = stream_blocks(n_pools, g->n, K, route == Route::kQueues && n_pools <= kFewPools);
+        kernel = route == Route::kDealt ? k_trace_stream<kCount, Route::kDealt> : k_trace_stream<kCount, Route::kQueues>;
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTraceBlock), 0, s, at<float>(bvh, L.header),
+                       at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), at<float4>(bvh, L.origins), dirs, g->n, K,
+                       cc, m_lo, m_hi, by_leaf ? 1 : 0, queues, vis_ray, totals);
 }
 
 // Enqueue the all-ray trace with its scratch at ws (256-byte aligned: the
@@ -1226,7 +1305,7 @@ extern "C" rv_status rv_trace_visibility_backward(const void *bvh, const rv_gaus
     }
     if (mem && n_pools > kAdjOnePoolWaves) {
         const auto kernel = n_pools > kFewPools ? k_adjoint_trace<false, true> : k_adjoint_trace<false, false>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)stream_blocks(n_pools, n, K)), dim3(kTraceBlock), 0, s,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)stream_blocks(n_pools, n, K, n_pools <= kFewPools)), dim3(kTraceBlock), 0, s,
                            at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), pools,
                            int64_t(0), n_pools, c, queues, grad_vis_ray, grad_vis_mean, vis_ray_fwd, grad_opacity,
                            grad_mean, grad_log_scale, sc);

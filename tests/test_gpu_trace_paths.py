@@ -65,3 +65,17 @@ def test_deep_walks_and_smallest_trees(n, K):
 def test_few_rays_of_a_large_tree():
     sc = scenes.make_object_scene(60_000, 1)
     _check(sc, 1, 1, "object-60000x1")
+
+
+# 10,000 pools are the last that get a wave each (24,000 with up to 256 Gaussians);
+# beyond, they are dealt in chunks of 64, the last one partial
+@pytest.mark.parametrize("n,K", [(10_000, 63), (10_000, 64), (256, 6000), (256, 6001), (257, 2003), (12_345, 61)])
+def test_dealt_pools(n, K):
+    _check(scenes.make_object_scene(n, 1), K, 1, f"object-{n}x{K}")
+
+
+def test_dealt_pools_of_a_dense_scene():
+    sc = scenes.make_cube_cloud(12_000, 0)
+    sc["log_scale"] += np.float32(1.0)
+    sc["opacity"] *= np.float32(0.1)
+    _check(sc, 64, 0, "dense-12000x64", sample=64)
