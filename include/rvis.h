@@ -326,11 +326,12 @@ rv_status rv_gather_probe(const void *table, int64_t n_records, int32_t rounds, 
  * clamp are not differentiated. Gradients are ACCUMULATED (+=) into the
  * caller's buffers with FP32 atomics: zero them first; the summation order,
  * hence the last bits, may vary between runs.
- * The call takes 256 + 48 n bytes of device scratch, stream-ordered on
- * `stream` (hipMallocAsync, released by hipFreeAsync after its launches), for
- * per-Gaussian accumulators and work-queue counters; if that allocation fails,
- * every term is added to the caller's buffers at once (same result up to the
- * summation order). Calls on different streams take separate scratch.
+ * With more than 1,024 rays the call takes 256 + 48 n bytes of device scratch,
+ * stream-ordered on `stream` (hipMallocAsync, released by hipFreeAsync after its
+ * launches), for per-Gaussian accumulators and work-queue counters; with fewer, or
+ * if that allocation fails, every term is added to the caller's buffers at once
+ * (same result up to the summation order). Calls on different streams take
+ * separate scratch.
  */
 rv_status rv_trace_visibility_backward(const void *bvh, const rv_gaussians *g, const float *dirs, int32_t K,
                                        const rv_trace_params *p, const float *grad_vis_ray,

@@ -699,14 +699,32 @@ __global__ __launch_bounds__(256) void k_sh_rows(const float *__restrict__ rows,
 // Waves of one launch that take a pool each: a dispatch counts its work-items in 32
 // bits, so one grid stays at 2^24 waves (2^30 work-items).
 constexpr int64_t kLaunchWaves = int64_t(1) << 24;
-// Up to this many pools every wave takes one pool (four blocks per CU, so that the
-// next node's words fit the registers): one pool / queues 293 / 361 us at 5,003 x 33
-// (2,607 pools), 309 / 404 us at 10,000 x 64, 784 / 697 us at 20,000 x 64.
-constexpr int64_t kAdjOnePoolWaves = 16000;
+// Up to so many pools every wave takes one (four blocks per CU, so that the next node's
+// words fit the registers); beyond, pools are dealt, and from kAdjDealtPools on they
+// come by queues. One / dealt in us with the forward's T: 286 / 322 at 5,003 x 33 (2,607
+// pools), surfaces 232 / 216 at 8,000 x 64 and 388 / 300 at 12,000 x 64, but 203 / 242 at
+// 2,000 x 500, whose rays are short. A ray that is walked twice is twice as long: 264 /
+// 301 at 4,000 x 64, 313 / 295 at 2,000 x 200, 625 / 476 (before either, 455) for eight
+// objects of 1,000 x 64. Dealt / queues: 169 / 302 (before, 281) at 250 x 8 x 512 (16,384
+// pools), but a cloud of 20,000 x 64 3,090 / 2,920.
+constexpr int64_t kAdjOnePoolWaves = 8000, kAdjOnePoolWavesShort = 16000, kAdjOnePoolWavesTwice = 5000;
+constexpr int64_t kAdjShortRays = 2048, kAdjDealtPools = 18000;
+inline Route adjoint_route(int64_t n_pools, int64_t n, bool twice) {
+    const int64_t one = twice ? kAdjOnePoolWavesTwice : n <= kAdjShortRays ? kAdjOnePoolWavesShort : kAdjOnePoolWaves;
+    return n_pools <= one ? Route::kOnePool : n_pools <= kAdjDealtPools ? Route::kDealt : Route::kQueues;
+}
+// Up to so many rays every term goes to the caller's arrays at once: the accumulators
+// are three launches more (two Gaussians x 64 54 us with them, 22 without).
+constexpr int64_t kAdjDirectRays = 1024;
 // Records per wave in LDS: as many as leave a CU five blocks; with chains a lane
 // each. A chip that is not filled (kFewPools) is bound by the waves' own time, which
-// chaining adds to: 697 / 784 us without / with at 20,000 x 64, the same at 50,000.
+// chaining adds to: 697 / 784 us without / with at 20,000 x 64, the same at 50,000. With
+// few Gaussians the same leaves come again and again: 343 / 250 us for 64 of deviation
+// 0.07 to 0.37 in a cube of side 2 x 4,096 directions, 1,466 / 1,332 for 500 x 1,000 (1,205
+// before), but 62.9 / 66.8 for 500 of 0.01 to 0.05 x 64.
 constexpr int kAdjStageChain = 64, kAdjStage = 88;
+constexpr int64_t kAdjChainGaussians = 1024;
+inline bool adjoint_chains(int64_t n_pools, int64_t n) { return n <= kAdjChainGaussians || n_pools > kFewPools; }
 constexpr int32_t kLinked = INT32_MIN;   // the leaf of a record that is not the head of its chain
 
 // What the adjoint works in (null: every term goes to the caller's arrays at once).
@@ -838,8 +856,8 @@ struct AdjStage {
 // with the same visits in the same order, recording dL/dalpha_j = -g T_final /
 // (1 - alpha_j) of each included, unclamped Gaussian. The source's own term
 // (through the ray origin) is summed over the ray.
-template <bool kOnePool, bool kChain>
-__global__ __launch_bounds__(kTraceBlock, kOnePool ? 4 : kStreamBlocksPerCu) void k_adjoint_trace(
+template <Route kRoute, bool kChain>
+__global__ __launch_bounds__(kTraceBlock, kRoute == Route::kOnePool ? 4 : kStreamBlocksPerCu) void k_adjoint_trace(
     const float *__restrict__ header, const float4 *__restrict__ nodes4, const float4 *__restrict__ rec, GridPools pools,
     int64_t first, int64_t n_pools, Cuts c,
     unsigned long long *__restrict__ queues, const float *__restrict__ grad_ray,
@@ -864,7 +882,8 @@ __global__ __launch_bounds__(kTraceBlock, kOnePool ? 4 : kStreamBlocksPerCu) voi
     AdjStage<kChain> stage;
     stage.s = stage_lds + wv;
     stage.n = 0;
-    std::conditional_t<kOnePool, RangeQueue, XcdQueue> queue;
+    constexpr bool kOnePool = kRoute == Route::kOnePool;
+    std::conditional_t<kOnePool, RangeQueue, std::conditional_t<kRoute == Route::kDealt, DealQueue, XcdQueue>> queue;
     if constexpr (kOnePool) {
         queue.next = first + xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + wv;
         queue.end = min(n_pools, queue.next + 1);
@@ -1285,13 +1304,13 @@ extern "C" rv_status rv_trace_visibility_backward(const void *bvh, const rv_gaus
     pools.n_chunks = (K + kStreamPoolS - 1) / kStreamPoolS;
     const int64_t n_pools = ((n + 63) / 64) * (int64_t)pools.n_chunks;
     // accumulators (stream-ordered, freed after the launches); without them every
-    // term goes to the caller's arrays at once
+    // term goes to the caller's arrays at once, by waves of one pool
     AdjScratch sc{};
     unsigned long long *queues = nullptr;
     const size_t off_acc = kQueueBytes, off_org = off_acc + (size_t)n * 8 * sizeof(float);
     const size_t bytes = off_org + (size_t)n * 4 * sizeof(float);
     void *mem = nullptr;
-    if (hipMallocAsync(&mem, bytes, s) != hipSuccess) {
+    if (n * (int64_t)K > kAdjDirectRays && hipMallocAsync(&mem, bytes, s) != hipSuccess) {
         mem = nullptr;
         (void)hipGetLastError();
     }
@@ -1303,19 +1322,22 @@ extern "C" rv_status rv_trace_visibility_backward(const void *bvh, const rv_gaus
         hipLaunchKernelGGL(k_fill_u32_wide, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0, s,
                            static_cast<uint32_t *>(mem), words, 0u);
     }
-    if (mem && n_pools > kAdjOnePoolWaves) {
-        const auto kernel = n_pools > kFewPools ? k_adjoint_trace<false, true> : k_adjoint_trace<false, false>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)stream_blocks(n_pools, n, K, n_pools <= kFewPools)), dim3(kTraceBlock), 0, s,
-                           at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), pools,
-                           int64_t(0), n_pools, c, queues, grad_vis_ray, grad_vis_mean, vis_ray_fwd, grad_opacity,
-                           grad_mean, grad_log_scale, sc);
-    } else {
+    const Route route = mem ? adjoint_route(n_pools, n, vis_ray_fwd == nullptr) : Route::kOnePool;
+    const bool chain = adjoint_chains(n_pools, n);
+    auto launch = [&](auto kernel, int64_t blocks, int64_t first) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTraceBlock), 0, s, at<float>(bvh, L.header),
+                           at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), pools, first, n_pools, c, queues,
+                           grad_vis_ray, grad_vis_mean, vis_ray_fwd, grad_opacity, grad_mean, grad_log_scale, sc);
+    };
+    if (route == Route::kOnePool) {
+        const auto kernel = chain ? k_adjoint_trace<Route::kOnePool, true> : k_adjoint_trace<Route::kOnePool, false>;
         for (int64_t first = 0; first < n_pools; first += kLaunchWaves)
-            hipLaunchKernelGGL((k_adjoint_trace<true, false>),
-                               dim3(grid_for(std::min(kLaunchWaves, n_pools - first), kWavesPerBlock)),
-                               dim3(kTraceBlock), 0, s, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4),
-                               at<float4>(bvh, L.leaf_rec), pools, first, n_pools, c, queues, grad_vis_ray, grad_vis_mean,
-                               vis_ray_fwd, grad_opacity, grad_mean, grad_log_scale, sc);
+            launch(kernel, grid_for(std::min(kLaunchWaves, n_pools - first), kWavesPerBlock), first);
+    } else {
+        const bool dealt = route == Route::kDealt;
+        const auto kernel = dealt ? (chain ? k_adjoint_trace<Route::kDealt, true> : k_adjoint_trace<Route::kDealt, false>)
+                                  : (chain ? k_adjoint_trace<Route::kQueues, true> : k_adjoint_trace<Route::kQueues, false>);
+        launch(kernel, stream_blocks(n_pools, n, K, !dealt && n_pools <= kFewPools), 0);
     }
     if (mem)
         hipLaunchKernelGGL(k_adjoint_add, dim3(grid_for(n, 256)), dim3(256), 0, s, at<float>(bvh, L.header),

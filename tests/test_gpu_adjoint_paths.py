@@ -64,3 +64,43 @@ def test_all_rays_in_one_call_and_in_parts():
         assert float((x.double() - y).norm() / y.norm()) <= 2 * 768 * 2.0 ** -24
         assert float(y.norm()) > 0
 
+
+
+# 1,024 rays are the last without accumulators, 1,024 Gaussians the last whose records
+# are chained in small launches; 5,000 pools (8,000 with the forward's T, 16,000 on up to
+# 2,048 Gaussians) the last that get a wave each, 18,000 the last that are dealt
+@pytest.mark.parametrize("n,K,use_fwd", [(256, 4, False), (257, 4, True), (1024, 312, False), (1024, 313, False),
+                                         (1025, 313, True), (2048, 500, True), (2048, 501, True), (2049, 243, True),
+                                         (4000, 285, False), (4000, 286, True)])
+def test_routes_of_small_launches(n, K, use_fwd):
+    test_routes_match_oracle_on_adjacent_gaussians(n, K, use_fwd)
+
+
+@pytest.mark.parametrize("n,K", [(300, 1200), (1000, 300), (1000, 1200)])
+def test_few_gaussians_in_one_call_and_in_parts(n, K):
+    """A dense cloud whose hits repeat few leaves (chained records, one pool per wave or
+    dealt) against the sum over single directions' calls in groups of three (1,024 rays
+    or fewer at n = 300: no accumulators; else unchained parts of the sum). About K hits
+    of a Gaussian's and K rays of its own, of either sign: 2 * 2 n K 2^-24 / sqrt(n K) of
+    the terms' 2-norm is far below 1e-4 of the sum's."""
+    sc = scenes.make_cube_cloud(n, 0)
+    sc["log_scale"] += np.float32(2.0)
+    sc["opacity"] *= np.float32(0.1)
+    dirs = scenes.fibonacci_dirs(K, False)
+    prm = TraceParams(T_min=0.0, dir_mode=0)
+    g = Gaussians.from_scene(sc)
+    bvh = build_bvh(g)
+    w = torch.from_numpy(np.random.default_rng(2).uniform(0.0, 1.0, (n, K)).astype(np.float32)).cuda()
+    fwd = trace_visibility(bvh, g, dirs, prm)[0]
+    whole = trace_visibility_backward(bvh, g, dirs, prm, grad_vis_ray=w, vis_ray_fwd=fwd)
+    again = trace_visibility_backward(bvh, g, dirs, prm, grad_vis_ray=w)
+    sums = [torch.zeros_like(x, dtype=torch.float64) for x in whole]
+    for a in range(0, K, 3):
+        part = trace_visibility_backward(bvh, g, dirs[a:a + 3], prm, grad_vis_ray=w[:, a:a + 3].contiguous(),
+                                         vis_ray_fwd=fwd[:, a:a + 3].contiguous())
+        for s, x in zip(sums, part):
+            s += x.double()
+    for x, y, s in zip(whole, again, sums):
+        assert float(s.norm()) > 0
+        assert float((x.double() - s).norm() / s.norm()) <= 1e-4
+        assert float((y.double() - s).norm() / s.norm()) <= 1e-4
