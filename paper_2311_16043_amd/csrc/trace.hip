@@ -131,7 +131,7 @@ struct RaySetup {
 // first, so that adjacent Gaussians share that XCD's L2; once the range is
 // spent it takes from the other ranges in turn, so no XCD idles while another
 // still holds work.
-// DealQueue: the pools are dealt to the XCDs in chunks of kDeal consecutive ones, with
+// DealQueue: the pools are dealt to the XCDs in chunks of kChunk consecutive ones, with
 // a counter each; a wave's first pool follows from its place in the grid, and it
 // leaves once its XCD's pools are spent. Chunks this small share a launch out as
 // evenly as taking from other ranges does, and a wave adds to one counter at its
@@ -166,9 +166,7 @@ struct XcdQueue {
     }
 };
 
-// Chunks of 4 / 16 / 64 pools: 484 / 471 / 402 us at 20,000 Gaussians x 64 (20,032
-// pools), 1,126 / 1,087 / 854 at 40,000 x 64.
-constexpr uint32_t kDeal = 64;
+template <uint32_t kChunk>
 struct DealQueue {
     unsigned long long *ctr;
     int64_t n_pools;
@@ -189,11 +187,15 @@ struct DealQueue {
             if (lane == __builtin_amdgcn_readfirstlane(lane)) t = held + (uint32_t)atomicAdd(ctr, 1ull);
             t = __builtin_amdgcn_readfirstlane(t);
         }
-        const uint32_t round = t / kDeal;
-        p = (int64_t)((round * kXcds + (xcd + round) % kXcds) * kDeal + t % kDeal);
+        const uint32_t round = t / kChunk;
+        p = (int64_t)((round * kXcds + (xcd + round) % kXcds) * kChunk + t % kChunk);
         return p < n_pools;
     }
 };
+
+// Of all-ray pools chunks of 4 / 16 / 64: 484 / 471 / 402 us at 20,000 Gaussians x 64
+// (20,032 pools), 1,126 / 1,087 / 854 at 40,000 x 64.
+using RayDeal = DealQueue<64>;
 
 struct RangeQueue {
     int64_t next, end;
@@ -210,7 +212,7 @@ template <class Queue>
 struct Refill {
     __device__ __forceinline__ bool now(uint64_t idle, int lanes) { return __popcll(idle) >= lanes || ~idle == 0; }
 };
-// From a DealQueue once the idle lanes have cost as much as about forty iterations of
+// From a RayDeal once the idle lanes have cost as much as about forty iterations of
 // the whole wave: the rays of one pool run side by side, and mixed with another's they
 // share fewer lines, which costs small launches more than idle lanes do unless the
 // pool's last rays are long. With 12 idle lanes / 1,024 / 2,048 / 4,096 / 8,192
@@ -219,7 +221,7 @@ struct Refill {
 // (deviations as under Route, divided by e) 6.1 / 6.3 / 6.2 / 6.1 / 6.6 / 7.5 ms at
 // 12,000 x 100 and, of 0.01 to 0.05, 1.06 / 1.12 / 1.18 / 1.33 / 1.59 / 1.39 ms.
 template <>
-struct Refill<DealQueue> {
+struct Refill<RayDeal> {
     static constexpr int kIdleMax = 2048;
     int idled = 0;
     __device__ __forceinline__ bool now(uint64_t idle, int) {
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_strea
         stream_rays<kCount, true>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x, vis_ray, cn, cl,
                                   ch);
     } else {
-        std::conditional_t<kRoute == Route::kDealt, DealQueue, XcdQueue> q;
+        std::conditional_t<kRoute == Route::kDealt, RayDeal, XcdQueue> q;
         q.init(queues, n_pools, blockIdx.x, gridDim.x);
         stream_rays<kCount, kRoute == Route::kDealt>(nodes4, rec, c, n, q, pools, stk + threadIdx.x, fifo + threadIdx.x,
                                                      vis_ray, cn, cl, ch);
@@ -522,15 +524,14 @@ __global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_strea
     }
 }
 
-// Listed rays in pools of kPoolS * 64 list entries. The list holds *count
-// entries when count is given (read on the device), else n_list.
-// out_by_value: T goes to out[ids[j]] (the list holds output positions, the
-// ray being id_offset + ids[j]); otherwise to out[j]. With kQueue the grid is
-// persistent and takes pools from per-XCD queues (queues[8], zero at launch),
-// each a contiguous eighth of the list, stealing from the others once its own
-// is spent; otherwise wave w takes the run of
-// pools [w R, (w + 1) R).
-template <bool kQueue>
+// Listed rays. The list holds *count entries when count is given (read on the
+// device), else n_list. out_by_value: T goes to out[ids[j]] (the list holds output
+// positions, the ray being id_offset + ids[j]); otherwise to out[j]. With kDealt and
+// kQueues the grid is persistent and takes pools of kPoolS * 64 entries, dealt or from
+// per-XCD queues (each a contiguous eighth of the list, stealing from the others once
+// its own is spent), through counters at queues (kQueueBytes, zero at launch). With
+// kOnePool wave w takes the run of pools [w R, (w + 1) R) of 64 entries.
+template <Route kRoute>
 __global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_list(
     const float *__restrict__ header, const float4 *__restrict__ nodes4, const float4 *__restrict__ rec, const float *__restrict__ mean,
     const float *__restrict__ normal, const float *__restrict__ log_scale, int64_t n, const float *__restrict__ dirs,
@@ -539,10 +540,12 @@ __global__ __launch_bounds__(kTraceBlock, kStreamBlocksPerCu) void k_trace_list(
     float *__restrict__ out) {
     __shared__ Pair stk[kStreamRing * kTraceBlock];
     __shared__ Pair fifo[kFifo * kTraceBlock];
+    constexpr bool kQueue = kRoute != Route::kOnePool;
     constexpr int kPool = kQueue ? kPoolS * 64 : 64;
     const int64_t total = count ? min<int64_t>(n_list, (int64_t)*count) : n_list;
     const int64_t n_pools = (total + kPool - 1) / kPool;
-    using Queue = typename std::conditional<kQueue, XcdQueue, RangeQueue>::type;
+    using Queue = std::conditional_t<!kQueue, RangeQueue,
+                                     std::conditional_t<kRoute == Route::kDealt, DealQueue<16>, XcdQueue>>;
     Queue q;
     if constexpr (kQueue) {
         q.init(queues, n_pools, blockIdx.x, gridDim.x);
@@ -883,7 +886,7 @@ __global__ __launch_bounds__(kTraceBlock, kRoute == Route::kOnePool ? 4 : kStrea
     stage.s = stage_lds + wv;
     stage.n = 0;
     constexpr bool kOnePool = kRoute == Route::kOnePool;
-    std::conditional_t<kOnePool, RangeQueue, std::conditional_t<kRoute == Route::kDealt, DealQueue, XcdQueue>> queue;
+    std::conditional_t<kOnePool, RangeQueue, std::conditional_t<kRoute == Route::kDealt, RayDeal, XcdQueue>> queue;
     if constexpr (kOnePool) {
         queue.next = first + xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + wv;
         queue.end = min(n_pools, queue.next + 1);
@@ -1095,6 +1098,12 @@ constexpr int64_t kListTargetWaves = 2048;
 
 }  // namespace
 
+// A queued list (the surrogate's fallback) is dealt in chunks of 16 pools, on up to
+// kFewPools rays by three blocks per CU. By queues and three blocks up to kFewPools pools /
+// so, the whole inference of 100,000 Gaussians x 64: 2,357 / 2,217 us with nothing listed,
+// 3,247 / 3,105 with 2 % of the queries, 4,204 / 3,857 with 45 %, 5,852 / 5,071 with all (5,771
+// before either); of 5,003 x 33 with 45 % 239 / 220. Trees from kDeepStreamGaussians keep the former
+// (1.2M x 8 with 45 % 10.6 / 12.4 ms).
 void launch_trace_list(const void *bvh, const rv_gaussians *g, const float *dirs, int K, const Cuts &c,
                        const int64_t *ids, int64_t n_list, const unsigned long long *count, int64_t id_offset,
                        bool out_by_value, float *out, unsigned long long *queues, hipStream_t stream) {
@@ -1103,21 +1112,21 @@ void launch_trace_list(const void *bvh, const rv_gaussians *g, const float *dirs
     const int64_t entries = queues ? kPoolS * 64 : 64, pools = (n_list + entries - 1) / entries;
     Cuts cc = c;
     cc.refill = refill_lanes(g->n);
-    if (queues) {
-        launch_clear_queues(queues, stream);
-        hipLaunchKernelGGL(k_trace_list<true>, dim3((unsigned)stream_blocks(pools, g->n, K, pools <= kFewPools)),
-                           dim3(kTraceBlock), 0, stream, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), g->mean,
+    auto launch = [&](auto kernel, int64_t blocks, int64_t run) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTraceBlock), 0, stream, at<float>(bvh, L.header),
+                           at<float4>(bvh, L.nodes4), at<float4>(bvh, L.leaf_rec), g->mean,
                            c.dir_mode ? g->normal : nullptr, g->log_scale, g->n, dirs, K, cc, ids, n_list, count,
-                           id_offset, out_by_value ? 1 : 0, (int64_t)0, queues, out);
+                           id_offset, out_by_value ? 1 : 0, run, queues, out);
+    };
+    if (queues) {
+        const bool deep = g->n >= kDeepStreamGaussians, dealt = pools <= kFewPools && !deep;
+        launch_clear_queues(queues, stream);
+        launch(dealt ? k_trace_list<Route::kDealt> : k_trace_list<Route::kQueues>,
+               stream_blocks(pools, g->n, K, pools * (deep ? 1 : kPoolS) <= kFewPools), 0);
         return;
     }
     const int64_t run = (pools + kListTargetWaves - 1) / kListTargetWaves;
-    const int64_t waves = (pools + run - 1) / run;
-    hipLaunchKernelGGL(k_trace_list<false>, dim3((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)),
-                       dim3(kTraceBlock), 0, stream, at<float>(bvh, L.header), at<float4>(bvh, L.nodes4),
-                       at<float4>(bvh, L.leaf_rec), g->mean,
-                       c.dir_mode ? g->normal : nullptr, g->log_scale, g->n, dirs, K, cc, ids, n_list, count, id_offset,
-                       out_by_value ? 1 : 0, run, (unsigned long long *)nullptr, out);
+    launch(k_trace_list<Route::kOnePool>, ((pools + run - 1) / run + kWavesPerBlock - 1) / kWavesPerBlock, run);
 }
 
 }  // namespace rv

@@ -5,6 +5,8 @@ import torch
 
 from paper_2311_16043_amd import Surrogate
 
+from test_gpu_surrogate import test_grid_inference_with_fallback_matches_tracer as _check_fallback
+
 pytestmark = pytest.mark.gpu
 
 
@@ -26,3 +28,10 @@ def test_gradient_of_a_batch_taken_twice(n):
     assert abs(float(l1) - float(l2)) <= 1e-6 * abs(float(l1))
     assert torch.isfinite(g1).all() and float(g1.norm()) > 0
     assert float((g1.double() - g2.double()).norm() / g1.double().norm()) <= max(1e-5, 8 * n * 2.0 ** -24)
+
+
+# the fallback list is dealt in chunks of 16 pools of 256 entries: less than a chunk, a
+# round of chunks and one entry, and a list that is given more blocks (2.56M queries on)
+@pytest.mark.parametrize("q0,qn,K", [(5, 3000, 32), (0, 2 * (8 * 16 * 256 + 1), 32), (0, 2_560_001, 160)])
+def test_dealt_fallback_lists(q0, qn, K):
+    _check_fallback(q0, qn, K)
