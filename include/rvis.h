@@ -123,7 +123,8 @@ const char *rv_version(void);
 /* Bytes of the BVH blob for n Gaussians (256-byte aligned sections). */
 size_t rv_bvh_bytes(int64_t n);
 
-/* Bytes of build scratch for n Gaussians. */
+/* Bytes of build scratch for n Gaussians: about 43.4 n, from 2^18 + 1 to 2^26
+ * Gaussians 83.4 n, and never less than for a smaller n. */
 size_t rv_build_workspace_bytes(int64_t n);
 
 /*

@@ -1130,7 +1130,7 @@ namespace {
 LeafArgs leaf_args(const rv_gaussians *g, void *bvh, const BvhLayout &L, void *ws, const BuildWsLayout &W) {
     LeafArgs a;
     a.in = Inputs{g->mean, g->quat, g->log_scale, g->opacity, g->normal};
-    a.packed = g->n > kPackFrom ? at<float4>(ws, W.packed) : nullptr;
+    a.packed = packs_inputs(g->n) ? at<float4>(ws, W.packed) : nullptr;
     a.perm = at<uint32_t>(bvh, L.perm);
     a.rec = at<float4>(bvh, L.leaf_rec);
     a.box = at<float>(bvh, L.leaf_box);

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -108,15 +109,24 @@ constexpr int kBoxBlock = 512;
 constexpr int kKeyWindow = 3 * kBoxBlock, kBoxWindow = 2 * kBoxBlock;
 // Largest power-of-two window of leaf boxes that a block of nodes builds.
 constexpr int kTopWindow = 8;
-// Above this many Gaussians the inputs of a leaf are gathered from packed records,
+// Above kPackFrom Gaussians the inputs of a leaf are gathered from packed records,
 // written while the means are read for their bounds: one 64-byte line in the
 // place of five partly used ones. Unpacked / packed: refit of 1.2M 211 / 178 us,
 // build of 300,000 169 / 167 us, of 130,000 123 / 125 us (the inputs then fit
-// the L2s).
-constexpr int64_t kPackFrom = int64_t(1) << 18;
+// the L2s). Above kPackTo (a scene of 20 GB with its tree) the records' memory counts
+// more.
+constexpr int64_t kPackFrom = int64_t(1) << 18, kPackTo = int64_t(1) << 26;
+inline bool packs_inputs(int64_t n) { return n > kPackFrom && n <= kPackTo; }
 
+// Bytes per Gaussian: 43.4, with packed inputs 83.4 (the sort alone needs 12.6). The
+// topology is written once the sort has ended, and the node boxes once every leaf is
+// prepared, so each shares the bytes of what is dead by then.
 struct BuildWsLayout {
-    size_t keys_tmp, vals_tmp, before, totals, bounds, box8, box64, box512, node_box, topo, packed, total;
+    size_t keys_tmp, vals_tmp, before, totals;   // sort; from keys_tmp on
+    size_t topo;
+    size_t packed;                               // inputs of the leaves, and from there on
+    size_t node_box;
+    size_t bounds, box8, box64, box512, total;
 };
 
 inline BuildWsLayout build_ws_layout(int64_t n) {
@@ -124,18 +134,20 @@ inline BuildWsLayout build_ws_layout(int64_t n) {
     size_t nn = (size_t)(n > 0 ? n : 1);
     const SortPlan plan = sort_plan((int64_t)nn);
     size_t off = 0;
-    W.keys_tmp = off; off = align_up(off + nn * 8);
+    W.keys_tmp = W.topo = off; off = align_up(off + nn * 8);
     W.vals_tmp = off; off = align_up(off + nn * 4);
     W.before = off; off = align_up(off + (size_t)plan.tiles * kDigits * 4);
     W.totals = off; off = align_up(off + (size_t)((plan.tiles + plan.group - 1) / plan.group) * kDigits * 4);
+    off = std::max(off, align_up(W.topo + nn * 16));
+    W.packed = W.node_box = off;
+    off = align_up(off + nn * (packs_inputs((int64_t)nn) ? 64 : 6 * sizeof(float)));
     W.bounds = off; off = align_up(off + kBoundsBlocks * 6 * sizeof(float));
     W.box8 = off; off = align_up(off + (nn + 7) / 8 * 6 * sizeof(float));
     W.box64 = off; off = align_up(off + (nn + 63) / 64 * 6 * sizeof(float));
     W.box512 = off; off = align_up(off + (nn + 511) / 512 * 6 * sizeof(float));
-    W.node_box = off; off = align_up(off + nn * 6 * sizeof(float));
-    W.topo = off; off = align_up(off + nn * 16);
-    W.packed = off; off = align_up(off + ((int64_t)nn > kPackFrom ? nn * 64 : 0));
     W.total = off;
+    // a workspace that holds n Gaussians holds fewer as well
+    if (n > kPackTo) W.total = std::max(W.total, build_ws_layout(kPackTo).total);
     return W;
 }
 
