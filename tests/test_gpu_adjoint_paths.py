@@ -79,10 +79,9 @@ def test_routes_of_small_launches(n, K, use_fwd):
 @pytest.mark.parametrize("n,K", [(300, 1200), (1000, 300), (1000, 1200)])
 def test_few_gaussians_in_one_call_and_in_parts(n, K):
     """A dense cloud whose hits repeat few leaves (chained records, one pool per wave or
-    dealt) against the sum over single directions' calls in groups of three (1,024 rays
-    or fewer at n = 300: no accumulators; else unchained parts of the sum). About K hits
-    of a Gaussian's and K rays of its own, of either sign: 2 * 2 n K 2^-24 / sqrt(n K) of
-    the terms' 2-norm is far below 1e-4 of the sum's."""
+    dealt) against the sum over calls of three directions each (1,024 rays or fewer at
+    n = 300: no accumulators). Up to 10^5 terms reach a Gaussian, and roundings of
+    FP32 sums of m terms grow as sqrt(m) 2^-24, 2 10^-5 of the sum: 10^-4 in the 2-norm."""
     sc = scenes.make_cube_cloud(n, 0)
     sc["log_scale"] += np.float32(2.0)
     sc["opacity"] *= np.float32(0.1)

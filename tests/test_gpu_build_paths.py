@@ -4,8 +4,10 @@ one-block sort and its item counts, the packed inputs, the sort's tile sizes,
 and trees whose ranges are long, far from their node, or all of one key."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
+from paper_2311_16043_amd import Gaussians, _lib, build_bvh, refit_bvh
 from workloads import scenes
 
 from test_gpu_build import _build, check_build
@@ -45,3 +47,32 @@ def test_build_all_equal_and_comb(n):
     sc["mean"] = (sc["mean"] * np.float32(2.0) ** (-2 - level)[:, None] * np.float32(0.25)
                   + np.float32(2.0) ** (-level)[:, None]).astype(np.float32)
     check_build(sc, f"comb-{n}")
+
+
+def _sections(A):
+    return {k: v for k, v in A.items() if k != "header"}
+
+
+@pytest.mark.parametrize("n", [100, 131_073, 262_145, 300_001])
+def test_no_normals_is_the_normal_0_0_1(n):
+    """Without normals (read directly, or above 2^18 Gaussians through the packed
+    records) every section holds what it holds with all normals (0, 0, 1), after a
+    build and after a refit to moved Gaussians, in a workspace sized for more."""
+    rng = np.random.default_rng(n)
+    sc = scenes.make_cube_cloud(n, 0)
+    ws = torch.empty(int(_lib.load().rv_build_workspace_bytes(n + 5000)), dtype=torch.uint8, device="cuda")
+    moved = (sc["mean"] + rng.normal(0.0, 0.05, sc["mean"].shape)).astype(np.float32)
+    up = np.tile(np.array([0.0, 0.0, 1.0], np.float32), (n, 1))
+    got = []
+    for normal in (None, up):
+        def gaussians(mean):
+            return Gaussians(torch.from_numpy(mean), *(torch.from_numpy(sc[k]) for k in ("quat", "log_scale", "opacity")),
+                             None if normal is None else torch.from_numpy(normal))
+        bvh = build_bvh(gaussians(sc["mean"]), ws)
+        built = bvh.arrays()
+        got.append((built, refit_bvh(bvh, gaussians(moved), ws).arrays()))
+    for a, b in zip(*got):
+        assert np.array_equal(a["header"][:13].view(np.uint32), b["header"][:13].view(np.uint32))
+        for k, v in _sections(a).items():
+            assert np.array_equal(v.view(np.uint32), b[k].view(np.uint32)), k
+    assert not np.array_equal(got[0][0]["leaf_boxes"], got[0][1]["leaf_boxes"])
