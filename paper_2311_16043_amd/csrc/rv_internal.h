@@ -42,9 +42,6 @@ constexpr float kBuildSigma = 3.0f;
 // Header floats: lo[3], hi[3] of the means; root box lo[3], hi[3]; n (as float bits) ...
 constexpr int kHeaderFloats = 16;
 
-// Child id of an unused or missed slot of a four-wide node as the traversal
-// reports it (leaves are ~m, internal nodes their binary id >= 0).
-constexpr int32_t kEmptyChild = INT32_MIN;
 // Bytes per compressed four-wide node (48 used).
 constexpr size_t kNode4Bytes = 64;
 // Leaf record, three float4 per sorted leaf: (mu, opacity), (W row 0,

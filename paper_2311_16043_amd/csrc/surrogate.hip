@@ -325,6 +325,9 @@ __device__ __forceinline__ void encode_tiles(const FwdArgs &a, int64_t s_base, i
 // are fetched before the barrier that its inputs wait for. 21.6 us at 8,192 samples,
 // against 18.9 + 20.6 us as two kernels that fetched weights after the barrier, read
 // the masks back from memory and encoded every sample in all eight waves.
+// Registers (227) leave a CU one block, so 8,320 samples take a second round; four whole
+// steps, those kernels / this one: 222 / 144 us at 1,024 samples, 260 / 170 at 8,192, 282 / 241
+// at 8,320, 341 / 273 at 16,384, 428 / 372 at 16,512, 583 / 488 at 32,768, 2,901 / 1,899 at 131,072.
 __global__ __launch_bounds__(kTrainWaves * 64, 16 / kTrainWaves) void k_mlp_train(FwdArgs a, const u32x4 *__restrict__ bwd,
                                                                                  uint16_t *__restrict__ dz) {
     constexpr int NT = kTrainNT;

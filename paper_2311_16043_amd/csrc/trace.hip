@@ -67,15 +67,18 @@ constexpr int kLeafMin = 32;
 // those out, and with few pools they also end further apart. 5 / 4 / 3 blocks:
 // 40.0 / 42.0 / 50.3 ms at 300,000 Gaussians x 256; 4.48 / 4.76 / 5.44 ms at
 // 100,000 x 128, 1.16 / 1.17 / 1.23 ms at 50,000 x 64, 774 / 744 / 743 us at
-// 30,000 x 64 (six: 43.8 ms at 300,000 x 256; all by XcdQueue). On large trees the fewer directions
-// a Gaussian has, the more Gaussians the pools in flight cover, and the tree they
-// touch outgrows the L2: 5 / 4 blocks on one surface of 3M Gaussians 110 / 94 ms x 16
-// and 407 / 353 x 64, of 1.2M 173 / 157 x 128; in 20 objects of 150,000 46.3 / 44.8
-// x 16, 168.4 / 169.9 x 64, 644 / 667 x 256 and 2,525 / 2,651 x 1,024 (six: 2,820).
-// The line lies where the one gains about ten times what the other loses.
+// 30,000 x 64 (six: 43.8 ms at 300,000 x 256; all by XcdQueue). On large trees the fewer
+// directions a Gaussian has, the more Gaussians the pools in flight cover, and the
+// tree they touch outgrows the L2: 5 / 4 blocks on one surface of 3M Gaussians 110 / 94 ms
+// x 16, 407 / 353 x 64 and 1,621 / 1,407 x 256, of 1.2M 173 / 156 x 128 and 686 / 625 x 512; in
+// 20 objects of 150,000 46.3 / 44.8 x 16, 168.4 / 169.9 x 64, 327 / 334 x 128, 643 / 664 x 256 and
+// 2,525 / 2,651 x 1,024 (six: 2,820). Nothing that the host knows tells one surface from
+// many objects; the line leaves the many directions of a composition's
+// pre-computation five blocks, at the price of one large surface's.
 constexpr int kStreamBlocksPerCu = 5, kStreamBlocksDeep = 4, kStreamBlocksFew = 3;
 constexpr int64_t kFewPools = 40000, kDeepStreamGaussians = int64_t(1) << 20;
 constexpr int kDeepStreamDirs = 96;
+
 // How a launch's waves come to their pools. The counters of XcdQueue, on few lines,
 // serve about one wave in 50 ns, and every wave adds to all eight to find them spent.
 //   kOnePool  every wave takes one pool and the hardware hands out the blocks; the
@@ -1092,8 +1095,12 @@ int64_t stream_blocks(int64_t n_pools, int64_t n, int K, bool few) {
 
 // Waves of the list kernel beyond which each wave takes a run of several pools of
 // 64 entries: few full waves end closer together than many that contend for the
-// caches. With 2,048 / 4,096 / 16,384 waves 1.58 / 1.74 / 1.96 ms for 1M random rays
-// (1.82 ms in pools of 256), 433 / 378 / 378 us for 200,000.
+// caches. With 2,048 / 4,096 / 16,384 waves, in ms, lists over 300,000 Gaussians x 256:
+// random and sorted 0.66 / 0.68 / 0.68 for 200,000 entries, 1.55 / 1.72 / 1.90 for 1M, 11.2 /
+// 12.7 / 12.5 for 10M, 31.3 / 31.7 / 31.6 for 30M; random 0.66 / 0.76 / 0.76 for 200,000,
+// 13.0 / 14.7 / 15.1 for 10M; consecutive 0.74 / 0.59 / 0.59 for 200,000, 1.94 / 1.78 / 1.68 for
+// 1M, 33.6 / 38.0 / 37.9 for 30M. Over 3M Gaussians x 64 sorted 6.3 / 6.6 / 6.2 for 1M, 116 / 121 /
+// 118 for 30M. (32,768 waves of pools of 256: 1.21, 1.84, 13.1, 32.4 for the first four.)
 constexpr int64_t kListTargetWaves = 2048;
 
 }  // namespace
@@ -1140,7 +1147,7 @@ extern "C" size_t rv_trace_workspace_bytes(int64_t n, int32_t K) {
 
 namespace {
 
-// The persistent all-ray traversal: clear the XCD queues (first 64 bytes of
+// The all-ray traversal: clear the XCD queues where they are used (kQueueBytes at
 // ws), then trace every ray (writing vis_ray when given, counters into totals
 // when counting).
 template <bool kCount>
