@@ -86,20 +86,24 @@ constexpr int kDeepStreamDirs = 96;
 //             block's last has ended.
 //   kDealt    a persistent grid takes the pools from DealQueue.
 //   kQueues   a persistent grid takes the pools from XcdQueue.
-// kOnePool / kDealt in us: surfaces 79 / 85 at 1,000 Gaussians x 600 (9,600 pools),
-// 207 / 173 at 10,000 x 64, 248 / 246 at 10,000 x 100, 468 / 386 at 20,000 x 64; a cloud
-// in which a ray crosses hundreds of Gaussians (10 % opaque, standard deviations 0.07 to
-// 0.37 of a side of 2) 12.5 / 11.7 ms at 10,000 x 64, 36.1 / 30.5 at 20,000 x 64. On up
+// kOnePool / kDealt in us, hemisphere directions: surfaces 79 / 85 at 1,000 Gaussians x 600
+// (9,600 pools), 207 / 172 at 10,000 x 64, 256 / 200 at 14,264 x 51, 468 / 343 at 20,000 x 64;
+// clouds 724 / 709 at 9,444 x 68, 1,471 / 1,149 at 12,000 x 100, and where a ray crosses
+// hundreds of Gaussians (a tenth as opaque, standard deviations 0.07 to 0.37 of a side
+// of 2) 16.5 / 15.4 ms at 12,000 x 64 (17.1 by queues, six blocks per CU), 36.1 / 30.6 at
+// 20,000 x 64 (32.5). With the same directions for all Gaussians every pool's rays run
+// side by side, and neither wins: a cloud of 9,905 x 82 706 / 760, of 12,000 x 64 763 / 723. On up
 // to 256 Gaussians rays are so short that even a counter each is in the way (150 / 212
 // at 64 x 20,000), and a tree that outgrows the caches wants its pools in order
 // (1,889 / 2,146 at 1.2M x 1). kDealt / kQueues: surfaces 390 / 422 at 24,000 x 64 and
 // 599 / 715 at 30,000 x 64, but clouds 1,414 / 1,334 at 12,000 x 128 and, as above with
-// deviations divided by e, 20.1 / 17.4 ms at 30,000 x 64.
+// deviations divided by e, 20.1 / 17.4 ms at 30,000 x 64 (lanes taking rays after 2,048
+// lane-iterations).
 enum class Route { kOnePool, kDealt, kQueues };
 constexpr int64_t kOnePoolWaves = 10000, kDealtPools = 24000, kFewGaussians = 256;
-inline Route all_ray_route(int64_t n_pools, int64_t n) {
+inline Route all_ray_route(int64_t n_pools, int64_t n, int dir_mode) {
     if (n_pools > kDealtPools) return Route::kQueues;
-    const bool dealt = n_pools > kOnePoolWaves && n > kFewGaussians && n < kDeepStreamGaussians;
+    const bool dealt = dir_mode == 1 && n_pools > kOnePoolWaves && n > kFewGaussians && n < kDeepStreamGaussians;
     return dealt ? Route::kDealt : Route::kOnePool;
 }
 
@@ -214,24 +218,40 @@ struct RangeQueue {
 template <class Queue>
 struct Refill {
     __device__ __forceinline__ bool now(uint64_t idle, int lanes) { return __popcll(idle) >= lanes || ~idle == 0; }
+    __device__ __forceinline__ void loaded(uint64_t, f3) {}
 };
-// From a RayDeal once the idle lanes have cost as much as about forty iterations of
-// the whole wave: the rays of one pool run side by side, and mixed with another's they
-// share fewer lines, which costs small launches more than idle lanes do unless the
-// pool's last rays are long. With 12 idle lanes / 1,024 / 2,048 / 4,096 / 8,192
-// lane-iterations / never, in us: surfaces 165 / 162 / 135 / 134 / 134 / 133 at 5,000
-// Gaussians x 128 and 502 / 576 / 599 / 571 / 511 / 502 at 30,000 x 64, a cloud
-// (deviations as under Route, divided by e) 6.1 / 6.3 / 6.2 / 6.1 / 6.6 / 7.5 ms at
-// 12,000 x 100 and, of 0.01 to 0.05, 1.06 / 1.12 / 1.18 / 1.33 / 1.59 / 1.39 ms.
+// From a RayDeal as the rays ask for. Rays of one pool that run side by side share
+// lines, and few of them are long: mixed with another pool's they share less, and the
+// long ones, which a small launch ends with, advance at the pace of a full wave. So a
+// wave whose lanes took like directions waits until no lane has a ray. Rays in all
+// directions share little and are long where the scene is dense: there lanes take new
+// ones once the idle ones have cost as much as sixteen iterations of the wave.
+// Waiting / with 1,024 / 2,048 / 4,096 idle lane-iterations, in us: surfaces 134 / 162 / 135 / 134
+// at 5,000 Gaussians x 128, 362 / - / 471 / 367 at 14,824 x 89; clouds in hemispheres about
+// random normals 1,390 / 1,149 / 1,266 / 1,330 at 12,000 x 100, 1,980 / 1,555 / 1,693 / 1,750 at
+// 20,000 x 64 and, with deviations as under Route divided by e, 5.5 / 4.7 / 4.8 / 4.7 ms at
+// 12,000 x 64.
 template <>
 struct Refill<RayDeal> {
-    static constexpr int kIdleMax = 2048;
+    static constexpr int kIdleMost = 1024;
     int idled = 0;
+    bool alike = true;   // the rays last taken run side by side
     __device__ __forceinline__ bool now(uint64_t idle, int) {
         idled += __popcll(idle);
-        if (idled < kIdleMax && ~idle != 0) return false;
+        if ((alike || idled < kIdleMost) && ~idle != 0) return false;
         idled = 0;
         return true;
+    }
+    // The lanes that took a ray of direction d. Of rays in all directions every
+    // fourth pair lies within 60 degrees; few lanes say nothing.
+    __device__ __forceinline__ void loaded(uint64_t lanes, f3 d) {
+        auto other = [](float x) {   // of the next lane or the one before
+            return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xb1, 0xf, 0xf, false));
+        };
+        const uint64_t pairs = lanes & (((lanes >> 1) & 0x5555555555555555ull) | ((lanes & 0x5555555555555555ull) << 1));
+        const int close = __popcll(__ballot(dot(d, mk(other(d.x), other(d.y), other(d.z))) > 0.5f) & pairs);
+        const int n = __popcll(pairs);
+        if (n >= 32) alike = 8 * close >= 5 * n;
     }
 };
 
@@ -277,6 +297,7 @@ __device__ __forceinline__ void stream_rays(const float4 *__restrict__ nodes4, c
         // refill idle lanes, moving on to further pools while lanes are idle
         uint64_t need = __ballot(wk.idle());
         if (!refill.now(need, c.refill)) need = 0;
+        const uint64_t empty = need;
         while (need != 0 && more) {
             if (next >= pool_n) {
                 int64_t p;
@@ -301,6 +322,7 @@ __device__ __forceinline__ void stream_rays(const float4 *__restrict__ nodes4, c
             next += __popcll(need);
             need = __ballot(wk.idle());
         }
+        if (empty != 0) refill.loaded(empty & ~need, d);
         if (__ballot(!wk.idle()) == 0) break;  // queue spent, every ray finished
 
         // node phase: one four-wide node per lane with traversal work and FIFO
@@ -1160,7 +1182,7 @@ void launch_trace_stream(const void *bvh, const rv_gaussians *g, const float *di
     auto *queues = static_cast<unsigned long long *>(ws);
     Cuts cc = c;
     cc.refill = refill_lanes(g->n);
-    const Route route = all_ray_route(n_pools, g->n);
+    const Route route = all_ray_route(n_pools, g->n, c.dir_mode);
     int64_t blocks = (n_pools + kWavesPerBlock - 1) / kWavesPerBlock;
     auto kernel = k_trace_stream<kCount, Route::kOnePool>;
     if (route != Route::kOnePool) {

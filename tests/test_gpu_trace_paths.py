@@ -79,3 +79,12 @@ def test_dealt_pools_of_a_dense_scene():
     sc["log_scale"] += np.float32(1.0)
     sc["opacity"] *= np.float32(0.1)
     _check(sc, 64, 0, "dense-12000x64", sample=64)
+
+
+def test_dealt_pools_of_rays_in_all_directions():
+    """Hemispheres about random normals: the lanes of a dealt wave take new rays while
+    others still walk."""
+    sc = scenes.make_cube_cloud(12_000, 0)
+    sc["log_scale"] += np.float32(1.0)
+    sc["opacity"] *= np.float32(0.1)
+    _check(sc, 64, 1, "dense-12000x64", sample=64)
