@@ -729,15 +729,18 @@ __global__ __launch_bounds__(256) void k_sh_rows(const float *__restrict__ rows,
 constexpr int64_t kLaunchWaves = int64_t(1) << 24;
 // Up to so many pools every wave takes one (four blocks per CU, so that the next node's
 // words fit the registers); beyond, pools are dealt, and from kAdjDealtPools on they
-// come by queues. One / dealt in us with the forward's T: 286 / 322 at 5,003 x 33 (2,607
-// pools), surfaces 232 / 216 at 8,000 x 64 and 388 / 300 at 12,000 x 64, but 203 / 242 at
-// 2,000 x 500, whose rays are short. A ray that is walked twice is twice as long: 264 /
-// 301 at 4,000 x 64, 313 / 295 at 2,000 x 200, 625 / 476 (before either, 455) for eight
-// objects of 1,000 x 64. Dealt / queues: 169 / 302 (before, 281) at 250 x 8 x 512 (16,384
-// pools), but a cloud of 20,000 x 64 3,090 / 2,920.
+// come by queues. One / dealt in us with the
+// forward's T: 286 / 322 at 5,003 x 33 (2,607 pools), surfaces 232 / 216 at 8,000 x 64 and 388 /
+// 300 at 12,000 x 64, but 203 / 242 at 2,000 x 500, whose rays are short; a cloud of 9,887 x
+// 75 1,407 / 1,346. A ray that is walked twice is twice as long: 264 / 301 at 4,000 x 64, 313 /
+// 295 at 2,000 x 200, 625 / 476 (before either, 455) for eight objects of 1,000 x 64. Dealt /
+// queues: 169 / 302 (before, 281) at 250 x 8 x 512 (16,384 pools), but a cloud of 20,000 x 64
+// 3,090 / 2,920. With the same directions for all Gaussians pools are not dealt: a cloud
+// of 8,935 x 79 1,094 / 1,250, of 6,647 x 69 walked twice 1,114 / 1,210.
 constexpr int64_t kAdjOnePoolWaves = 8000, kAdjOnePoolWavesShort = 16000, kAdjOnePoolWavesTwice = 5000;
 constexpr int64_t kAdjShortRays = 2048, kAdjDealtPools = 18000;
-inline Route adjoint_route(int64_t n_pools, int64_t n, bool twice) {
+inline Route adjoint_route(int64_t n_pools, int64_t n, bool twice, int dir_mode) {
+    if (dir_mode == 0) return n_pools <= kAdjOnePoolWavesShort ? Route::kOnePool : Route::kQueues;
     const int64_t one = twice ? kAdjOnePoolWavesTwice : n <= kAdjShortRays ? kAdjOnePoolWavesShort : kAdjOnePoolWaves;
     return n_pools <= one ? Route::kOnePool : n_pools <= kAdjDealtPools ? Route::kDealt : Route::kQueues;
 }
@@ -946,10 +949,16 @@ __global__ __launch_bounds__(kTraceBlock, kRoute == Route::kOnePool ? 4 : kStrea
     // wave-uniform pool state
     int next = 0, pool_n = 0;
     bool more = true;
+    // (rays that are walked twice leave lanes idle twice as long: those are taken as on a
+    // filled chip)
+    Refill<RayDeal> patient;
+    Refill<XcdQueue> filled;
 
     for (uint32_t round = 1;; ++round) {
         uint64_t need = __ballot(wk.idle());
-        if (__popcll(need) < c.refill && ~need != 0) need = 0;
+        const bool take = kRoute == Route::kDealt && vis_fwd ? patient.now(need, c.refill) : filled.now(need, c.refill);
+        if (!take) need = 0;
+        const uint64_t empty = need;
         while (need != 0 && more) {
             if (next >= pool_n) {
                 int64_t p;
@@ -979,6 +988,7 @@ __global__ __launch_bounds__(kTraceBlock, kRoute == Route::kOnePool ? 4 : kStrea
             next += __popcll(need);
             need = __ballot(wk.idle());
         }
+        if (kRoute == Route::kDealt && vis_fwd && empty != 0) patient.loaded(empty & ~need, d);
         if (__ballot(!wk.idle()) == 0) break;
 
         if (wk.can_walk()) {
@@ -1360,7 +1370,7 @@ extern "C" rv_status rv_trace_visibility_backward(const void *bvh, const rv_gaus
         hipLaunchKernelGGL(k_fill_u32_wide, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0, s,
                            static_cast<uint32_t *>(mem), words, 0u);
     }
-    const Route route = mem ? adjoint_route(n_pools, n, vis_ray_fwd == nullptr) : Route::kOnePool;
+    const Route route = mem ? adjoint_route(n_pools, n, vis_ray_fwd == nullptr, c.dir_mode) : Route::kOnePool;
     const bool chain = adjoint_chains(n_pools, n);
     auto launch = [&](auto kernel, int64_t blocks, int64_t first) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTraceBlock), 0, s, at<float>(bvh, L.header),
